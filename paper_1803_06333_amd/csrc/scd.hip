@@ -28,28 +28,38 @@ namespace snap {
 // coordinate i is under way, the nonzeros and scalars of i+1, the ptr entries of i+2 and the order
 // entry of i+3 are requested too, all independent of each other; only the reads of v, which must be
 // as late as possible, stay in the visit they belong to.  (x[c], the norms and the labels are not
-// written by other coordinates' updates.)  Up to SMALL_ROUNDS nonzeros per lane travel this way and
-// are scattered from registers; longer coordinates take the rest in plain loops.
-// SMALL_ROUNDS is 1 when no small coordinate of the data is longer than a wavefront, else 4.
-template <int SMALL_ROUNDS>
+// written by other coordinates' updates.)  The part of the step that does not need v is taken while the
+// gather is under way.  What was requested for later visits is waited for ahead of the scatter: memory
+// operations are waited for in the order of their issue, so that waiting for it at the top of the next
+// visit would also wait for the atomics of this one (3700 of the 6700 cycles of a visit with 200
+// nonzeros) before the next gather has even been asked for.
+//
+// Up to ROUNDS nonzeros per lane travel in registers and are scattered from there; longer coordinates
+// take the rest in loops of TAIL_ROUNDS independent loads.  ROUNDS is the smallest of 1, 4 and 16 that holds
+// the longest coordinate (16 from 257 nonzeros on; columns of 465 nonzeros that took every fifth and
+// later round through dependent loads cost 28000 cycles a visit).
+//
+// One wavefront per workgroup: a compute unit issues about one scattered atomic per six cycles, so
+// the four wavefronts of a workgroup queued on one unit while most of the 256 units had none.
+constexpr int SMALL_TPB = WAVE;
+constexpr int TAIL_ROUNDS = 8;
+
+template <int ROUNDS>
 struct SmallCoord {
     int64_t c, s0, s1;            // coordinate, its range in the chunk's arrays
-    uint32_t raw[SMALL_ROUNDS];   // index words of this lane: nonzeros s0 + j * 64 + lane
-    float a[SMALL_ROUNDS];
+    uint32_t raw[ROUNDS];         // index words of this lane: nonzeros s0 + j * 64 + lane
+    float a[ROUNDS];
     float xc, nc, yc;
 };
 
-template <int KIND, int SMALL_ROUNDS>
-__global__ void __launch_bounds__(TPB)
+template <int KIND, int ROUNDS>
+__global__ void __launch_bounds__(SMALL_TPB)
 k_scd_small(ChunkView cv, const uint32_t* __restrict__ order, int64_t n_small, const float* __restrict__ y,
             float* __restrict__ x, float* v, const float* __restrict__ norms, StepParams sp, int64_t n_waves) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t wave0 = ((int64_t)blockIdx.x * TPB + threadIdx.x) / WAVE;
-    if (wave0 >= n_waves) return;
+    const int lane = threadIdx.x;
+    const int64_t wave0 = blockIdx.x;
+    constexpr uint32_t IDX_MASK = KIND == K_PRIMAL_LOGISTIC ? ~LABEL_BIT : 0xFFFFFFFFu;
     // n_waves wavefronts walk the epoch order round-robin: at most n_waves coordinates in flight.
-    // What a visit requests for later coordinates is only touched in the next visit, arithmetic on
-    // it included (the wait for a value sits before its first use: an addition right after the load
-    // would put the wait there, and the requests would again be served one after the other).
     auto order_entry = [&](int64_t wid) -> uint32_t { return wid < n_small ? order[wid] : 0u; };
     auto ptr_pair = [&](int64_t c, int64_t& p0, int64_t& p1) {
         p0 = p1 = 0;
@@ -58,12 +68,12 @@ k_scd_small(ChunkView cv, const uint32_t* __restrict__ order, int64_t n_small, c
             p1 = cv.ptr[c + 1];
         }
     };
-    auto fetch = [&](int64_t c, int64_t s0, int64_t s1) -> SmallCoord<SMALL_ROUNDS> {
-        SmallCoord<SMALL_ROUNDS> q;
+    auto fetch = [&](int64_t c, int64_t s0, int64_t s1) -> SmallCoord<ROUNDS> {
+        SmallCoord<ROUNDS> q;
         q.c = c, q.s0 = s0, q.s1 = s1;
         q.xc = q.nc = q.yc = 0.0f;
 #pragma unroll
-        for (int j = 0; j < SMALL_ROUNDS; ++j) {
+        for (int j = 0; j < ROUNDS; ++j) {
             const int64_t k = s0 + j * WAVE + lane;
             q.raw[j] = 0u;
             q.a[j] = 0.0f;
@@ -84,7 +94,7 @@ k_scd_small(ChunkView cv, const uint32_t* __restrict__ order, int64_t n_small, c
     int64_t cB = coord_at(wave0 + n_waves, order_entry(wave0 + n_waves));   // its nonzeros are requested next
     uint32_t entryA = order_entry(wave0 + 2 * n_waves);                     // its ptr pair is read next
     int64_t p0B, p1B;
-    SmallCoord<SMALL_ROUNDS> cur;
+    SmallCoord<ROUNDS> cur;
     {
         const int64_t c = coord_at(wave0, order_entry(wave0));
         int64_t p0, p1;
@@ -95,13 +105,13 @@ k_scd_small(ChunkView cv, const uint32_t* __restrict__ order, int64_t n_small, c
     for (int64_t wid = wave0; wid < n_small; wid += n_waves) {
         // this visit's requests
         const int64_t c = cur.c, s0 = cur.s0, s1 = cur.s1;
-        uint32_t r[SMALL_ROUNDS];
-        float vv[SMALL_ROUNDS], yy[SMALL_ROUNDS];
-        bool have[SMALL_ROUNDS];
+        uint32_t r[ROUNDS];
+        float vv[ROUNDS], yy[ROUNDS];
+        bool have[ROUNDS];
 #pragma unroll
-        for (int j = 0; j < SMALL_ROUNDS; ++j) {
+        for (int j = 0; j < ROUNDS; ++j) {
             have[j] = s0 + j * WAVE + lane < s1;
-            r[j] = cur.raw[j] & (KIND == K_PRIMAL_LOGISTIC ? ~LABEL_BIT : 0xFFFFFFFFu);
+            r[j] = cur.raw[j] & IDX_MASK;
             vv[j] = yy[j] = 0.0f;
             if (have[j]) {
                 vv[j] = load_shared(v, r[j]);
@@ -109,35 +119,68 @@ k_scd_small(ChunkView cv, const uint32_t* __restrict__ order, int64_t n_small, c
                 if (KIND == K_PRIMAL_LOGISTIC) yy[j] = (cur.raw[j] & LABEL_BIT) ? -1.0f : 1.0f;
             }
         }
-        const SmallCoord<SMALL_ROUNDS> nxt = fetch(cB, p0B - cv.nnz_base, p1B - cv.nnz_base);
+        SmallCoord<ROUNDS> nxt = fetch(cB, p0B - cv.nnz_base, p1B - cv.nnz_base);
         const int64_t cA = coord_at(wid + 2 * n_waves, entryA);
         int64_t p0A, p1A;
         ptr_pair(cA, p0A, p1A);
-        const uint32_t entry3 = order_entry(wid + 3 * n_waves);
+        uint32_t entry3 = order_entry(wid + 3 * n_waves);
+        // nothing moves across: the requests first, then what can be computed while they are under way
+        __builtin_amdgcn_sched_barrier(0);
+        StepPrep prep = prepare_step<KIND>(cur.xc, cur.nc, cur.yc, sp);
+        asm volatile("" : "+v"(prep.a), "+v"(prep.b), "+v"(prep.c));
+        __builtin_amdgcn_sched_barrier(0);
 
         float g = 0.0f, h = 0.0f;
         // (these nonzeros stay in registers for the scatter pass)
 #pragma unroll
-        for (int j = 0; j < SMALL_ROUNDS; ++j)
+        for (int j = 0; j < ROUNDS; ++j)
             if (have[j]) accumulate<KIND>(cur.a[j], vv[j], yy[j], g, h);
-        for (int64_t k = s0 + SMALL_ROUNDS * WAVE + lane; k < s1; k += WAVE) {
-            uint32_t rr;
-            float yk;
-            decode<KIND>(cv.idx[k], rr, yk, y);
-            accumulate<KIND>(cv.val[k], load_shared(v, rr), yk, g, h);
+        for (int64_t k0 = s0 + ROUNDS * WAVE + lane; k0 < s1; k0 += TAIL_ROUNDS * WAVE) {
+            uint32_t rr[TAIL_ROUNDS];
+            float at[TAIL_ROUNDS], yt[TAIL_ROUNDS], vt[TAIL_ROUNDS];
+#pragma unroll
+            for (int j = 0; j < TAIL_ROUNDS; ++j) {        // (past the end: the lane's first nonzero with value 0)
+                const int64_t k = k0 + j * WAVE;
+                const bool on = k < s1;
+                rr[j] = cv.idx[on ? k : k0];
+                at[j] = on ? cv.val[k] : 0.0f;
+            }
+#pragma unroll
+            for (int j = 0; j < TAIL_ROUNDS; ++j) {
+                decode<KIND>(rr[j], rr[j], yt[j], y);
+                vt[j] = load_shared(v, rr[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < TAIL_ROUNDS; ++j) accumulate<KIND>(at[j], vt[j], yt[j], g, h);
         }
         g = wave_sum(g);
         if (KIND == K_PRIMAL_LOGISTIC) h = wave_sum(h);
-        float mult = 0.0f;
-        if (lane == 0) x[c] = take_step<KIND>((double)g, (double)h, cur.xc, cur.nc, cur.yc, sp, mult);
-        mult = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mult), 0));   // lane 0's, without an LDS round trip
+        // every lane takes the same step
+        float mult;
+        const float xn = finish_step<KIND>((double)g, (double)h, cur.xc, cur.nc, cur.yc, prep, sp, mult);
+        if (lane == 0) x[c] = xn;
+        // the requests of this visit for later ones have arrived by now: take them over ahead of the atomics
+#pragma unroll
+        for (int j = 0; j < ROUNDS; ++j) asm volatile("" : "+v"(nxt.raw[j]), "+v"(nxt.a[j]));
+        asm volatile("" : "+v"(nxt.xc), "+v"(nxt.nc), "+v"(nxt.yc), "+v"(p0A), "+v"(p1A), "+v"(entry3));
+        __builtin_amdgcn_sched_barrier(0);
         if (mult != 0.0f) {
 #pragma unroll
-            for (int j = 0; j < SMALL_ROUNDS; ++j)
+            for (int j = 0; j < ROUNDS; ++j)
                 if (have[j]) unsafeAtomicAdd(v + r[j], mult * cur.a[j]);
-            for (int64_t k = s0 + SMALL_ROUNDS * WAVE + lane; k < s1; k += WAVE) {
-                const uint32_t rr = cv.idx[k] & (KIND == K_PRIMAL_LOGISTIC ? ~LABEL_BIT : 0xFFFFFFFFu);
-                unsafeAtomicAdd(v + rr, mult * cv.val[k]);
+            for (int64_t k0 = s0 + ROUNDS * WAVE + lane; k0 < s1; k0 += TAIL_ROUNDS * WAVE) {
+                uint32_t rr[TAIL_ROUNDS];
+                float at[TAIL_ROUNDS];
+#pragma unroll
+                for (int j = 0; j < TAIL_ROUNDS; ++j) {
+                    const int64_t k = k0 + j * WAVE;
+                    const bool on = k < s1;
+                    rr[j] = cv.idx[on ? k : k0] & IDX_MASK;
+                    at[j] = on ? cv.val[k] : 0.0f;
+                }
+#pragma unroll
+                for (int j = 0; j < TAIL_ROUNDS; ++j)
+                    if (k0 + j * WAVE < s1) unsafeAtomicAdd(v + rr[j], mult * at[j]);
             }
         }
         cur = nxt;
@@ -384,13 +427,14 @@ static int launch_kind(snap_handle* h, const ChunkView& cv, const snap_handle::C
         int64_t waves = std::min<int64_t>(ck.n_small, 256 * 32);
         if (h->inflight_nnz > 0)
             waves = std::min<int64_t>(waves, std::max<int64_t>(1, (int64_t)((double)h->inflight_nnz / h->avg_small_len)));
-        const dim3 grid((unsigned)((waves + WAVES_PER_WG - 1) / WAVES_PER_WG));
-        if (h->max_small_len <= WAVE)
-            hipLaunchKernelGGL((k_scd_small<KIND, 1>), grid, dim3(TPB), 0, h->compute, cv, order, ck.n_small, h->y, h->x,
-                               h->v, h->norms, sp, waves);
-        else
-            hipLaunchKernelGGL((k_scd_small<KIND, 4>), grid, dim3(TPB), 0, h->compute, cv, order, ck.n_small, h->y, h->x,
-                               h->v, h->norms, sp, waves);
+        const dim3 grid((unsigned)waves);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(SMALL_TPB), 0, h->compute, cv, order, ck.n_small, h->y, h->x, h->v, h->norms,
+                               sp, waves);
+        };
+        if (h->max_small_len <= WAVE) launch(k_scd_small<KIND, 1>);
+        else if (h->max_small_len <= 4 * WAVE) launch(k_scd_small<KIND, 4>);
+        else launch(k_scd_small<KIND, 16>);
     }
     SNAP_HIP(hipGetLastError());
     return SNAP_OK;

@@ -89,31 +89,54 @@ __device__ __forceinline__ float primal_step(double Gf, double Hf, double rinv, 
     return xn;
 }
 
-// The scalar step.  Returns the new value of the coordinate; `mult` receives the multiplier of a_j
-// that is added to v: the change actually applied to the fp32 coordinate (times y_i in the hinge
-// dual), so that v keeps tracking A x as closely as fp32 allows.
+// The scalar step, in two parts.  What depends on the coordinate alone (its value, norm, label) is prepared
+// first: in the dual forms that is two fp64 logarithms or a division, 400 ... 1600 cycles that the wavefront
+// of a short coordinate takes while it waits for its entries of v instead of between their sum and the
+// scatter.  finish_step returns the new value of the coordinate; `mult` receives the multiplier of a_j
+// that is added to v: the change actually applied to the fp32 coordinate (times y_i in the dual forms),
+// so that v keeps tracking A x as closely as fp32 allows.
+struct StepPrep {
+    double a, b, c;     // ridge: curvature, 1 / (curvature + lambda); dual: see prepare_step
+};
+
 template <int KIND>
-__device__ __forceinline__ float take_step(double g, double h, float xc, float norm, float yc,
-                                           const StepParams& sp, float& mult) {
+__device__ __forceinline__ StepPrep prepare_step(float xc, float norm, float yc, const StepParams& sp) {
+    StepPrep p{0.0, 0.0, 0.0};
+    if (KIND == K_PRIMAL_RIDGE) {
+        p.a = (double)norm * sp.inv_n;
+        p.b = 1.0 / (p.a + sp.lambda);
+    } else if (KIND == K_DUAL && sp.dual_logistic) {
+        // -n dD/da = ln(a/(1-a)) + m,  -n d2D/da2 = 1/(a(1-a)) + q: one Newton step, kept inside (0,1)
+        // (1 - a is exact in fp64: a is an fp32 number of at least 2^-20)
+        const double a = (double)xc, q = (double)norm * sp.inv_lam_n;
+        p.a = log(a) - log(1.0 - a);
+        p.b = 1.0 / (1.0 / (a * (1.0 - a)) + q);
+        p.c = (double)yc * sp.inv_lam_n;                  // m = y_i x_i.v / (lambda n)
+    } else if (KIND == K_DUAL) {
+        p.b = norm == 0.0f ? 0.0 : sp.lam_n / (double)norm;
+        p.c = (double)yc * sp.inv_lam_n;
+    }
+    return p;
+}
+
+template <int KIND>
+__device__ __forceinline__ float finish_step(double g, double h, float xc, float norm, float yc, const StepPrep& p,
+                                             const StepParams& sp, float& mult) {
     float xn;
-    if (KIND == K_PRIMAL_RIDGE || KIND == K_PRIMAL_LOGISTIC) {
-        const double Hf = (KIND == K_PRIMAL_RIDGE ? (double)norm : h) * sp.inv_n;
+    if (KIND == K_PRIMAL_RIDGE) {
+        xn = primal_step(g * sp.inv_n, p.a, p.b, xc, sp, mult);
+    } else if (KIND == K_PRIMAL_LOGISTIC) {
+        const double Hf = h * sp.inv_n;
         xn = primal_step(g * sp.inv_n, Hf, 1.0 / (Hf + sp.lambda), xc, sp, mult);
     } else {
         double anew;
         if (sp.dual_logistic) {
-            // -n dD/da = ln(a/(1-a)) + m,  -n d2D/da2 = 1/(a(1-a)) + q: one Newton step, kept inside (0,1)
-            const double a = (double)xc;
-            const double m = (double)yc * g * sp.inv_lam_n, q = (double)norm * sp.inv_lam_n;
-            anew = a - (log(a) - log1p(-a) + m) / (1.0 / (a * (1.0 - a)) + q);
+            anew = (double)xc - (p.a + p.c * g) * p.b;
             anew = anew < ALPHA_EPS ? ALPHA_EPS : (anew > 1.0 - ALPHA_EPS ? 1.0 - ALPHA_EPS : anew);
         } else if (norm == 0.0f) {
             anew = 1.0;                                   // empty row: dD/dalpha = 1/n > 0
         } else {
-            // (fp64 divisions are long instruction sequences on the one lane that takes the step, and
-            // with few rows in flight the step is on the critical path: one is left)
-            const double m = (double)yc * g * sp.inv_lam_n;   // y_i x_i.w
-            anew = (double)xc + (1.0 - m) * sp.lam_n / (double)norm;
+            anew = (double)xc + (1.0 - p.c * g) * p.b;
             anew = anew < 0.0 ? 0.0 : (anew > 1.0 ? 1.0 : anew);
         }
         anew = (double)xc + sp.damping * (anew - (double)xc);   // stays inside the box
@@ -121,6 +144,12 @@ __device__ __forceinline__ float take_step(double g, double h, float xc, float n
         mult = (float)(((double)xn - (double)xc) * (double)yc);
     }
     return xn;
+}
+
+template <int KIND>
+__device__ __forceinline__ float take_step(double g, double h, float xc, float norm, float yc,
+                                           const StepParams& sp, float& mult) {
+    return finish_step<KIND>(g, h, xc, norm, yc, prepare_step<KIND>(xc, norm, yc, sp), sp, mult);
 }
 
 template <int KIND>
