@@ -68,10 +68,11 @@ struct Sorter {              // scratch of the radix sort, sized for max_m coord
 struct Reducer {             // scratch for deterministic fp64 reductions
     double* partial = nullptr;   // [REDUCE_BLOCKS * 4]
     double* result = nullptr;    // [8] device
-    double* host = nullptr;      // [8] pinned host, mapped into the device's address space
+    double* host = nullptr;      // [9] pinned host, mapped into the device's address space
     double* host_mapped = nullptr;   // the device's pointer to the same memory
 };
 constexpr int REDUCE_BLOCKS = 1024;
+constexpr int MOVED_WORD = 8;    // entry of Reducer::host that receives the count of coordinates that moved (dual forms)
 
 }  // namespace snap
 
@@ -118,6 +119,9 @@ struct snap_handle {
     uint32_t* ticket = nullptr;       // work-item counter
     uint32_t* status = nullptr;       // device error flag
     int64_t max_large = 0;
+    // dual forms: popular features whose updates are summed per wavefront (null: none), count of moved rows
+    uint32_t* hot_tag = nullptr;
+    uint32_t* moved = nullptr;
 
     // chunks (resident: one chunk covering everything)
     struct Chunk { int64_t c0, c1, nnz0, nnz1, n_small, n_large, n_items, l0, l1; };   // [l0,l1): its range of large_list
@@ -257,6 +261,9 @@ int make_permutation(snap_handle* h, uint64_t seed, uint32_t chunk, int64_t c0, 
 
 // scd.hip
 int scd_run_chunk(snap_handle* h, const ChunkView& cv, const snap_handle::Chunk& ck, const uint32_t* order);
+int hot_setup(snap_handle* h);       // popular features of the dual forms
+void hot_reset(snap_handle* h);      // the model is no longer the last epoch's
+void hot_free(snap_handle* h);
 
 // stream.hip: run fn on every chunk in order (resident data: one chunk, no copies).  Streaming:
 // double-buffered copies on the copy stream overlap fn's work on the compute stream.

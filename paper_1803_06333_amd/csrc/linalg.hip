@@ -502,7 +502,7 @@ static int fetch_results(snap_handle* h, int count) {
 int reducer_alloc(Reducer& r) {
     SNAP_HIP(hipMalloc(&r.partial, 2 * REDUCE_BLOCKS * sizeof(double)));
     SNAP_HIP(hipMalloc(&r.result, 8 * sizeof(double)));
-    SNAP_HIP(hipHostMalloc(&r.host, 8 * sizeof(double), hipHostMallocMapped));
+    SNAP_HIP(hipHostMalloc(&r.host, 9 * sizeof(double), hipHostMallocMapped));
     SNAP_HIP(hipHostGetDevicePointer((void**)&r.host_mapped, r.host, 0));
     return SNAP_OK;
 }

@@ -191,6 +191,359 @@ k_scd_small(ChunkView cv, const uint32_t* __restrict__ order, int64_t n_small, c
     }
 }
 
+// ---- short rows with popular features (dual forms): several rows per wavefront -----------------
+// The memory side performs the atomics on one 128-byte line one request after the other, 12.7 ns each, two
+// neighbouring lines 24, however many lanes a request carries.  Rows of a text-like corpus all hold the same
+// few features: while every row moves (the first epochs of the hinge form) an epoch waits 48 ms per
+// million rows for the two hottest lines.  So a wavefront takes R consecutive rows of the epoch
+// order at once and adds their updates to the popular features in LDS; they go out, one request per line, when
+// R / 2 rows have moved since the last time (most visits move no row in later epochs) and at the end.  The
+// wavefront's own gathers see what is pending.  The rows in flight stay as many: fewer wavefronts.  (At R
+// rows instead of R / 2 the epochs take 10 % less and the gap after the first one is five times as large.)
+//
+// A row has S places (32, 64 or 256 lanes of one or four registers), longer rows take the rest in plain loops.  The
+// sums of all rows are taken together: each exchange step halves the registers instead of repeating the whole
+// reduction per row, and lane l ends up with the sum of row row_of(l).  The steps of the rows are then taken
+// side by side, each lane that of its row.
+//
+// Popular features: one tag per slot of a direct-mapped table, the most frequent feature of a sample of the
+// rows (hot_setup).  LDS sums are fp64, rounded once: ds_add_f64 takes 39 cycles per wavefront, ds_add_f32 193.
+//
+// 1 M hinge rows of 50 nonzeros over 100 000 Zipf(1.1) features, 500 rows in flight, epochs from zero: 52.5, 12.0,
+// 7.1, 5.6, 4.6 ms with single rows, 9.2, 7.6, 5.7, 4.9, 4.5 ms this way.  Also measured, on easier labels (48.0, 11.5,
+// 4.4 ms with single rows): the popular entries of v read once per visit into LDS 10.5, 7.2, 5.4 ms (the loads
+// queue at the same lines), returned by the additions 11.9, 8.7, 6.5 ms, sent out at every visit 7.3, 8.4, 5.9 ms.
+constexpr int HOT_SLOTS = 512;
+constexpr uint32_t HOT_NONE = 0xFFFFFFFFu;
+constexpr int HOT_SAMPLE = 4096;
+__device__ __forceinline__ uint32_t hot_slot(uint32_t r) { return (r ^ (r >> 9)) & (HOT_SLOTS - 1); }
+
+template <int S, int R>
+struct MergeShape {
+    static constexpr int ROWS = R;                           // rows of a visit
+    static constexpr int REGS = ROWS * S / WAVE;
+    static constexpr int PER_ROW = S > WAVE ? S / WAVE : 1;  // registers of a row
+    __device__ static __forceinline__ int row_of(int lane) { return S == 32 ? 2 * (lane & (ROWS / 2 - 1)) + (lane >> 5) : lane & (ROWS - 1); }
+    __device__ static __forceinline__ int lane_of(int row) { return S == 32 ? (row >> 1) + 32 * (row & 1) : row; }
+    // value of the row that register j of this lane belongs to, from the lanes that hold the rows' values
+    __device__ static __forceinline__ int spread(int x, int j, bool upper) {
+        if (S == 32) return upper ? __builtin_amdgcn_readlane(x, 32 + j) : __builtin_amdgcn_readlane(x, j);
+        return __builtin_amdgcn_readlane(x, j / PER_ROW);
+    }
+};
+
+template <int DPP>
+__device__ __forceinline__ float dpp_move(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), DPP, 0xF, 0xF, false));
+}
+// lanes with `bit` keep b and hand a over, the others the other way round: one register for two sums
+template <int DPP>
+__device__ __forceinline__ float fold_pair(float a, float b, bool bit) {
+    return (bit ? b : a) + dpp_move<DPP>(bit ? a : b);
+}
+
+// p[j] = this lane's part of register j's row(s); returns the whole sum of row row_of(lane)
+template <int S, int R>
+__device__ __forceinline__ float sum_rows(const float (&p)[MergeShape<S, R>::REGS], int lane) {
+    constexpr int QUAD_SWAP_1 = 0xB1, QUAD_SWAP_2 = 0x4E, ROW_ROR_4 = 0x124, ROW_ROR_8 = 0x128;
+    constexpr int NP = MergeShape<S, R>::REGS / MergeShape<S, R>::PER_ROW;
+    float q[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        q[i] = p[i * MergeShape<S, R>::PER_ROW];
+#pragma unroll
+        for (int k = 1; k < MergeShape<S, R>::PER_ROW; ++k) q[i] += p[i * MergeShape<S, R>::PER_ROW + k];
+    }
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
+    float x;
+    if constexpr (NP == 8) {
+        const float t0 = fold_pair<QUAD_SWAP_1>(q[0], q[1], b0), t1 = fold_pair<QUAD_SWAP_1>(q[2], q[3], b0);
+        const float t2 = fold_pair<QUAD_SWAP_1>(q[4], q[5], b0), t3 = fold_pair<QUAD_SWAP_1>(q[6], q[7], b0);
+        const float u0 = fold_pair<QUAD_SWAP_2>(t0, t1, b1), u1 = fold_pair<QUAD_SWAP_2>(t2, t3, b1);
+        x = fold_pair<ROW_ROR_4>(u0, u1, b2);              // (each part travels to one lane of the other kind)
+    } else if constexpr (NP == 2) {
+        x = fold_pair<QUAD_SWAP_1>(q[0], q[1], b0);
+        x += dpp_move<QUAD_SWAP_2>(x);
+        x += dpp_move<ROW_ROR_4>(x);
+    } else {
+        static_assert(NP == 4, "two, four or eight sums");
+        const float t0 = fold_pair<QUAD_SWAP_1>(q[0], q[1], b0), t1 = fold_pair<QUAD_SWAP_1>(q[2], q[3], b0);
+        x = fold_pair<QUAD_SWAP_2>(t0, t1, b1);
+        x += dpp_move<ROW_ROR_4>(x);
+    }
+    x += dpp_move<ROW_ROR_8>(x);
+    auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
+    if (S != 32) {
+        auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
+    }
+    return x;
+}
+
+// moved: [0] rows whose coordinate moved, [1] wavefronts that are done; the last one writes the count
+// to host memory and clears both for the next epoch.
+template <int S, int R>
+__global__ void __launch_bounds__(WAVE)
+k_scd_merge(ChunkView cv, const uint32_t* __restrict__ order, int64_t n_small, const float* __restrict__ y,
+            float* __restrict__ x, float* v, const float* __restrict__ norms, StepParams sp, int64_t n_waves,
+            const uint32_t* __restrict__ hot_tag, uint32_t* moved, uint32_t* moved_out) {
+    using Shape = MergeShape<S, R>;
+    constexpr int ROWS = Shape::ROWS, REGS = Shape::REGS, PER_ROW = Shape::PER_ROW;
+    __shared__ uint32_t s_tag[HOT_SLOTS];
+    __shared__ double s_acc[HOT_SLOTS];
+    const int lane = threadIdx.x;
+    const bool upper = lane >= 32;
+    const int row = Shape::row_of(lane);
+    const bool owner = lane == Shape::lane_of(row);
+    uint32_t tag[HOT_SLOTS / WAVE];
+#pragma unroll
+    for (int i = 0; i < HOT_SLOTS / WAVE; ++i) {
+        tag[i] = hot_tag[i * WAVE + lane];
+        s_tag[i * WAVE + lane] = tag[i];
+        s_acc[i * WAVE + lane] = 0.0;
+    }
+    __syncthreads();
+
+    struct Rows {
+        int64_t c, s0;                // this lane's row: coordinate, first nonzero in the chunk's arrays
+        int len;
+        uint32_t raw[REGS];
+        float a[REGS];
+        float xc, nc, yc;
+    };
+    auto order_entry = [&](int64_t g) -> uint32_t { return g * ROWS + row < n_small ? order[g * ROWS + row] : 0u; };
+    auto coord_at = [&](int64_t g, uint32_t entry) -> int64_t { return g * ROWS + row < n_small ? cv.c0 + (int64_t)entry : -1; };
+    auto ptr_pair = [&](int64_t c, int64_t& p0, int64_t& p1) {
+        p0 = p1 = 0;
+        if (c >= 0) {
+            p0 = cv.ptr[c];
+            p1 = cv.ptr[c + 1];
+        }
+    };
+    auto place = [&](int j) -> int { return S == 32 ? (lane & 31) : (j % PER_ROW) * WAVE + lane; };
+    auto first_of = [&](int64_t s0, int j) -> int64_t {
+        const uint32_t lo = (uint32_t)Shape::spread((int)(uint32_t)s0, j, upper);
+        const int hi = Shape::spread((int)(s0 >> 32), j, upper);
+        return (int64_t)(((uint64_t)(uint32_t)hi << 32) | lo);
+    };
+    auto fetch = [&](int64_t c, int64_t p0, int64_t p1) -> Rows {
+        Rows q;
+        q.c = c, q.s0 = c >= 0 ? p0 - cv.nnz_base : 0, q.len = (int)(p1 - p0);
+        q.xc = q.nc = q.yc = 0.0f;
+#pragma unroll
+        for (int j = 0; j < REGS; ++j) {
+            const int64_t k = first_of(q.s0, j) + place(j);
+            const int len = Shape::spread(q.len, j, upper);
+            q.raw[j] = 0u;
+            q.a[j] = 0.0f;
+            if (place(j) < len) {
+                q.raw[j] = cv.idx[k];
+                q.a[j] = cv.val[k];
+            }
+        }
+        if (c >= 0) {
+            q.xc = x[c];
+            q.nc = norms[c];
+            q.yc = y[c];
+        }
+        return q;
+    };
+    const int64_t wave0 = blockIdx.x;
+    const int64_t n_visits = (n_small + ROWS - 1) / ROWS;
+    uint32_t n_moved = 0;
+    int64_t cB = coord_at(wave0 + n_waves, order_entry(wave0 + n_waves));
+    uint32_t entryA = order_entry(wave0 + 2 * n_waves);
+    int64_t p0B, p1B;
+    Rows cur;
+    {
+        const int64_t c = coord_at(wave0, order_entry(wave0));
+        int64_t p0, p1;
+        ptr_pair(c, p0, p1);
+        ptr_pair(cB, p0B, p1B);
+        cur = fetch(c, p0, p1);
+    }
+    uint32_t pending = 0;                                  // rows whose updates of popular features still sit in LDS
+    auto flush = [&]() {
+        // (one wavefront: its LDS operations are performed in the order of their issue)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        double t[HOT_SLOTS / WAVE];
+#pragma unroll
+        for (int i = 0; i < HOT_SLOTS / WAVE; ++i) t[i] = s_acc[i * WAVE + lane];
+#pragma unroll
+        for (int i = 0; i < HOT_SLOTS / WAVE; ++i)
+            if (t[i] != 0.0) {
+                s_acc[i * WAVE + lane] = 0.0;
+                unsafeAtomicAdd(v + tag[i], (float)t[i]);
+            }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        pending = 0;
+    };
+    for (int64_t g = wave0; g < n_visits; g += n_waves) {
+        float vv[REGS];
+        bool have[REGS], hot[REGS];
+#pragma unroll
+        for (int j = 0; j < REGS; ++j) {
+            have[j] = place(j) < Shape::spread(cur.len, j, upper);
+            hot[j] = have[j] && s_tag[hot_slot(cur.raw[j])] == cur.raw[j];
+        }
+#pragma unroll
+        for (int j = 0; j < REGS; ++j) vv[j] = have[j] ? load_shared(v, cur.raw[j]) : 0.0f;
+        Rows nxt = fetch(cB, p0B, p1B);
+        const int64_t cA = coord_at(g + 2 * n_waves, entryA);
+        int64_t p0A, p1A;
+        ptr_pair(cA, p0A, p1A);
+        uint32_t entry3 = order_entry(g + 3 * n_waves);
+        // nothing moves across: the requests first, then what can be computed while they are under way
+        __builtin_amdgcn_sched_barrier(0);
+        StepPrep prep = prepare_step<K_DUAL>(cur.xc, cur.nc, cur.yc, sp);
+        asm volatile("" : "+v"(prep.a), "+v"(prep.b), "+v"(prep.c));
+        __builtin_amdgcn_sched_barrier(0);
+
+        float part[REGS];
+#pragma unroll
+        for (int j = 0; j < REGS; ++j) part[j] = cur.a[j] * (hot[j] ? vv[j] + (float)s_acc[hot_slot(cur.raw[j])] : vv[j]);
+        float sum = sum_rows<S, R>(part, lane);
+        const bool longer = __ballot(cur.len > S) != 0;
+        if (longer) {
+            for (int q = 0; q < ROWS; ++q) {
+                const int l = Shape::lane_of(q), len = __builtin_amdgcn_readlane(cur.len, l);
+                if (len <= S) continue;
+                const int64_t s0 = ((int64_t)__builtin_amdgcn_readlane((int)(cur.s0 >> 32), l) << 32) |
+                                   (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)cur.s0, l);
+                float t = 0.0f;
+                for (int k = S + lane; k < len; k += WAVE) t += cv.val[s0 + k] * load_shared(v, cv.idx[s0 + k]);
+                t = wave_sum(t);
+                if (row == q) sum += t;
+            }
+        }
+        float mult;
+        const float xn = finish_step<K_DUAL>((double)sum, 0.0, cur.xc, cur.nc, cur.yc, prep, sp, mult);
+        if (cur.c < 0) mult = 0.0f;
+        if (owner && cur.c >= 0) x[cur.c] = xn;
+        const uint64_t movers = __ballot(owner && mult != 0.0f);
+        n_moved += (uint32_t)__popcll(movers);
+        // what was requested for later visits has arrived by now: take it over ahead of the atomics
+#pragma unroll
+        for (int j = 0; j < REGS; ++j) asm volatile("" : "+v"(nxt.raw[j]), "+v"(nxt.a[j]));
+        asm volatile("" : "+v"(nxt.xc), "+v"(nxt.nc), "+v"(nxt.yc), "+v"(p0A), "+v"(p1A), "+v"(entry3));
+        __builtin_amdgcn_sched_barrier(0);
+        if (movers != 0) {
+#pragma unroll
+            for (int j = 0; j < REGS; ++j) {
+                const float mj = __int_as_float(Shape::spread(__float_as_int(mult), j, upper));
+                if (have[j] && mj != 0.0f) {
+                    if (hot[j]) unsafeAtomicAdd(&s_acc[hot_slot(cur.raw[j])], (double)(mj * cur.a[j]));
+                    else unsafeAtomicAdd(v + cur.raw[j], mj * cur.a[j]);
+                }
+            }
+            if (longer) {
+                for (int q = 0; q < ROWS; ++q) {
+                    const int l = Shape::lane_of(q), len = __builtin_amdgcn_readlane(cur.len, l);
+                    const float mq = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mult), l));
+                    if (len <= S || mq == 0.0f) continue;
+                    const int64_t s0 = ((int64_t)__builtin_amdgcn_readlane((int)(cur.s0 >> 32), l) << 32) |
+                                       (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)cur.s0, l);
+                    for (int k = S + lane; k < len; k += WAVE) unsafeAtomicAdd(v + cv.idx[s0 + k], mq * cv.val[s0 + k]);
+                }
+            }
+            pending += (uint32_t)__popcll(movers);
+            if (pending >= ROWS / 2) flush();
+        }
+        cur = nxt;
+        cB = cA;
+        p0B = p0A;
+        p1B = p1A;
+        entryA = entry3;
+    }
+    if (pending != 0) flush();
+    if (lane == 0) {
+        // the addition has been performed before the arrival is counted (it returns the old value)
+        const uint32_t before = atomicAdd(&moved[0], n_moved);
+        uint32_t one = 1u;
+        asm volatile("" : "+v"(one) : "v"(before));
+        if (atomicAdd(&moved[1], one) == (uint32_t)n_waves - 1u) {
+            const uint32_t total = atomicExch(&moved[0], 0u);
+            __hip_atomic_store(&moved[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(moved_out, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+}
+
+// Features of a sample of the rows: counts, then the most frequent feature of every slot.
+__global__ void __launch_bounds__(WAVE)
+k_hot_count(const int64_t* __restrict__ ptr, const uint32_t* __restrict__ idx, int64_t m, int64_t small_max, int samples,
+            uint32_t* __restrict__ freq) {
+    const int64_t c = (int64_t)blockIdx.x * m / samples;
+    const int64_t s0 = ptr[c], s1 = ptr[c + 1];
+    if (s1 - s0 > small_max) return;
+    for (int64_t k = s0 + threadIdx.x; k < s1; k += WAVE) atomicAdd(freq + idx[k], 1u);
+}
+
+// best[slot] = count << 32 | ~feature; best[HOT_SLOTS] = the largest count.  A feature is taken if the sampled rows hold
+// line_least entries on its 128-byte line of v: a line in the table costs one request per R rows that moved.
+__global__ void k_hot_pick(const uint32_t* __restrict__ freq, int64_t len, uint32_t line_least, unsigned long long* __restrict__ best) {
+    constexpr int LINE = 128 / sizeof(float);
+    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < len; r += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t n = freq[r];
+        if (n == 0) continue;
+        const int64_t l0 = r & ~(int64_t)(LINE - 1), l1 = min(len, l0 + LINE);
+        uint32_t on_line = 0;
+        for (int64_t q = l0; q < l1; ++q) on_line += freq[q];
+        if (on_line < line_least) continue;
+        atomicMax(best + hot_slot((uint32_t)r), ((unsigned long long)n << 32) | (0xFFFFFFFFu - (uint32_t)r));
+        atomicMax(best + HOT_SLOTS, (unsigned long long)n);
+    }
+}
+
+__global__ void k_hot_tags(const unsigned long long* __restrict__ best, uint32_t* __restrict__ tag) {
+    for (int s = threadIdx.x; s < HOT_SLOTS; s += blockDim.x)
+        tag[s] = best[s] ? 0xFFFFFFFFu - (uint32_t)(best[s] & 0xFFFFFFFFu) : HOT_NONE;
+}
+
+// Creation, dual forms on resident sparse data: find the popular features.  Where no feature is in an eighth of
+// the rows the lines of v are not contended and every row goes alone.
+int hot_setup(snap_handle* h) {
+    if (h->kind != K_DUAL || h->dense || h->streaming || h->m < HOT_SAMPLE || h->vlen < 1 || h->nnz_small < 1) return SNAP_OK;
+    uint32_t* freq = nullptr;
+    unsigned long long *best = nullptr, top = 0;
+    auto find = [&]() -> int {
+        SNAP_HIP(hipMalloc(&freq, (size_t)h->vlen * sizeof(uint32_t)));
+        SNAP_HIP(hipMalloc(&best, (HOT_SLOTS + 1) * sizeof(*best)));
+        SNAP_HIP(hipMalloc(&h->hot_tag, HOT_SLOTS * sizeof(uint32_t)));
+        SNAP_HIP(hipMalloc(&h->moved, 2 * sizeof(uint32_t)));
+        SNAP_TRY(fill_zero(freq, (size_t)h->vlen * sizeof(uint32_t), h->compute));
+        SNAP_TRY(fill_zero(best, (HOT_SLOTS + 1) * sizeof(*best), h->compute));
+        SNAP_TRY(fill_zero(h->moved, 2 * sizeof(uint32_t), h->compute));
+        hipLaunchKernelGGL(k_hot_count, dim3(HOT_SAMPLE), dim3(WAVE), 0, h->compute, h->ptr, h->idx, h->m, h->small_max, HOT_SAMPLE, freq);
+        hipLaunchKernelGGL(k_hot_pick, dim3((unsigned)std::min<int64_t>(1024, (h->vlen + 255) / 256)), dim3(256), 0, h->compute, freq,
+                           h->vlen, (uint32_t)(HOT_SAMPLE / 8), best);
+        hipLaunchKernelGGL(k_hot_tags, dim3(1), dim3(256), 0, h->compute, best, h->hot_tag);
+        SNAP_HIP(hipGetLastError());
+        SNAP_HIP(hipMemcpyAsync(&top, best + HOT_SLOTS, sizeof(top), hipMemcpyDeviceToHost, h->compute));
+        SNAP_HIP(hipStreamSynchronize(h->compute));
+        return SNAP_OK;
+    };
+    const int rc = find();
+    (void)hipStreamSynchronize(h->compute);
+    (void)hipFree(freq);
+    (void)hipFree(best);
+    SNAP_TRY(rc);
+    if (top * 8 < (unsigned long long)HOT_SAMPLE) hot_free(h);
+    hot_reset(h);
+    return SNAP_OK;
+}
+
+void hot_reset(snap_handle* h) { reinterpret_cast<volatile uint32_t*>(h->red.host + MOVED_WORD)[0] = 0xFFFFFFFFu; }
+
+void hot_free(snap_handle* h) {
+    (void)hipFree(h->hot_tag);
+    (void)hipFree(h->moved);
+    h->hot_tag = h->moved = nullptr;
+}
+
 // ---- large coordinates: segments, two phases, ticket order -------------------------------------
 // Everything the workgroups of one coordinate exchange (partial sums, arrival count, the published
 // step) goes through device-scope atomic operations, which are performed at the level of the
@@ -427,6 +780,28 @@ static int launch_kind(snap_handle* h, const ChunkView& cv, const snap_handle::C
         int64_t waves = std::min<int64_t>(ck.n_small, 256 * 32);
         if (h->inflight_nnz > 0)
             waves = std::min<int64_t>(waves, std::max<int64_t>(1, (int64_t)((double)h->inflight_nnz / h->avg_small_len)));
+        if constexpr (KIND == K_DUAL) {
+            // Several rows per wavefront where popular features are contended for: eight while at least half of the
+            // rows move (by the count of the last epoch that kept one; 0xFFFFFFFF: none yet), four down to one row in 32,
+            // then single rows, whose visits are shorter (figures at k_scd_merge).  With fewer than 32 (24) wavefronts
+            // left the atomics of a compute unit, 7.7 ns per scattered lane, take longer than the contended lines
+            // (60 013 logistic rows of 23 nonzeros, 54 in flight: 1.9 ms single, 2.2 ms with R = 4, 2.9 with R = 8).
+            const uint32_t last = reinterpret_cast<volatile uint32_t*>(h->red.host + MOVED_WORD)[0];
+            const int64_t moving = last == 0xFFFFFFFFu ? ck.n_small : (int64_t)last;
+            const int rows = moving * 2 >= ck.n_small && waves >= 256 && h->avg_small_len <= WAVE ? 8 : 4;
+            if (h->hot_tag && moving * 32 >= ck.n_small && waves >= 96) {
+                const dim3 grid((unsigned)(waves / rows));
+                auto launch = [&](auto kernel) {
+                    hipLaunchKernelGGL(kernel, grid, dim3(WAVE), 0, h->compute, cv, order, ck.n_small, h->y, h->x, h->v, h->norms, sp,
+                                       (int64_t)grid.x, h->hot_tag, h->moved, reinterpret_cast<uint32_t*>(h->red.host_mapped + MOVED_WORD));
+                };
+                if (h->avg_small_len > WAVE) launch(k_scd_merge<256, 4>);
+                else if (h->max_small_len <= 32) rows == 8 ? launch(k_scd_merge<32, 8>) : launch(k_scd_merge<32, 4>);
+                else rows == 8 ? launch(k_scd_merge<64, 8>) : launch(k_scd_merge<64, 4>);
+                SNAP_HIP(hipGetLastError());
+                return SNAP_OK;
+            }
+        }
         const dim3 grid((unsigned)waves);
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, grid, dim3(SMALL_TPB), 0, h->compute, cv, order, ck.n_small, h->y, h->x, h->v, h->norms,

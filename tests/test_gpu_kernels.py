@@ -1,0 +1,74 @@
+"""GPU: kernels and dispatch branches that serve a range of sizes, at the edges of that range, against the oracle
+or a plain fp64 computation of the same quantity."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1803_06333_amd as snap
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def zipf_rows(lengths, d, seed, s=1.1):
+    """CSR arrays: row i holds lengths[i] distinct columns of popularity rank^-s, unit rows."""
+    rng = np.random.default_rng(seed)
+    p = np.arange(1, d + 1, dtype=np.float64) ** -s
+    p /= p.sum()
+    name = rng.permutation(d)                              # every second row: popularity does not follow the column number
+    cols, ptr = [], np.zeros(len(lengths) + 1, dtype=np.int64)
+    for i, k in enumerate(lengths):
+        c = rng.choice(d, size=min(d, 2 * k + 8), p=p)
+        c = np.unique(c)[:k] if k else c[:0]
+        cols.append(np.sort(name[c] if i % 2 else c))
+        ptr[i + 1] = ptr[i] + cols[-1].size
+    idx = np.concatenate(cols).astype(np.int32)
+    val = (np.abs(rng.standard_normal(idx.size)) + 0.05).astype(np.float32)
+    for i in range(len(lengths)):
+        v = val[ptr[i]:ptr[i + 1]]
+        if v.size:
+            v /= np.linalg.norm(v)
+    return ptr, idx, val
+
+
+def row_lengths(kind, n, rng):
+    if kind == "to32":
+        return rng.integers(1, 33, n)
+    if kind == "to64":
+        return rng.integers(20, 65, n)
+    if kind == "tails64":                                  # a few rows longer than the places of a row, and empty ones
+        k = rng.integers(8, 60, n)
+        k[::97], k[5::211] = rng.integers(65, 400, k[::97].size), 0
+        return k
+    k = rng.integers(65, 257, n)                           # "tails256"
+    k[::101] = rng.integers(257, 700, k[::101].size)
+    return k
+
+
+@pytest.mark.parametrize("loss", ["hinge", "logistic"])
+@pytest.mark.parametrize("kind,n", [("to32", 4096), ("to64", 4103), ("tails64", 5001), ("tails256", 4099)])
+@pytest.mark.parametrize("in_flight", [100, 300])          # four and eight rows per wavefront
+def test_rows_with_popular_features_keep_the_shared_vector_and_reach_the_optimum(kind, n, loss, in_flight):
+    d, lam = 6_000, 60.0 / n
+    rng = np.random.default_rng(11)
+    ptr, idx, val = zipf_rows(row_lengths(kind, n, rng), d, 12)
+    w = rng.standard_normal(d)
+    y = np.where([(val[a:b] * w[idx[a:b]]).sum() >= 0 for a, b in zip(ptr, ptr[1:])], 1.0, -1.0).astype(np.float32)
+    nnz = int(ptr[-1])
+    s = snap.Solver("csr", n, d, ptr, idx, val, y, loss, lam, max_inflight_nnz=in_flight * nnz // n)
+    A = np.zeros(d)
+    for e in range(40):
+        s.epoch(e)
+        if e in (0, 1, 5):
+            alpha = s.model()[1].astype(np.float64)
+            assert alpha.min() >= 0.0 and alpha.max() <= 1.0
+            A[:] = 0.0
+            np.add.at(A, idx, val.astype(np.float64) * np.repeat(y * alpha, np.diff(ptr)))
+            assert np.linalg.norm(s.shared() - A) <= 1e-4 * np.linalg.norm(A)
+    o = oracle.Solver(oracle.Matrix("csr", n, d, ptr, idx, val), y, loss, lam)
+    for e in range(40):
+        o.epoch(e)
+    P, D = s.objective(want_dual=True)
+    assert P - D >= -1e-6 * abs(P)
+    assert abs(D - o.dual()) <= 1e-3 * abs(o.dual()), (D, o.dual())
