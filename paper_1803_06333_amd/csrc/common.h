@@ -160,6 +160,7 @@ struct snap_handle {
     bool unit_values = false;         // every stored value is 1.0: no per-row value arrays
     int64_t n_groups = 0, n_pad = 0;  // n_pad: row stride of the per-group row maps (multiple of 8)
     int64_t* gbounds_host = nullptr;  // [n_groups+1]
+    int64_t* gbounds_dev = nullptr;   // the same on the device (resident maps)
     int* ghot_host = nullptr;         // [n_groups] number of hot (LDS-accumulated) ranks per group
     int* gk64_host = nullptr;         // [n_groups] of those, the leading ranks that keep two 64-bit sums (the rest: one packed word)
     bool gpack = false;               // packed ranks in use (logistic loss)
@@ -283,6 +284,7 @@ int group_search_advance(snap_handle* h, GroupSearch* s, const int64_t* hptr, co
 int group_search_end(snap_handle* h, GroupSearch* s, const int64_t* hptr, std::vector<int64_t>& bounds);
 void group_search_free(GroupSearch* s);
 int grouped_epoch(snap_handle* h);
+int grouped_shared(snap_handle* h);  // v = A x by the resident row maps
 int grouped_dots(snap_handle* h);    // gdot[c] = inner product of coordinate c with loss'(v), by row passes
 std::vector<int64_t> group_order(uint64_t seed, int64_t n_groups);   // visiting order of the groups for a seed
 void grouped_free(snap_handle* h);

@@ -72,3 +72,47 @@ def test_rows_with_popular_features_keep_the_shared_vector_and_reach_the_optimum
     P, D = s.objective(want_dual=True)
     assert P - D >= -1e-6 * abs(P)
     assert abs(D - o.dual()) <= 1e-3 * abs(o.dual()), (D, o.dual())
+
+
+def one_hot_columns(n, sizes, seed, missing, weighted):
+    """CSC arrays of one-hot fields (a share of the rows without a category), group bounds."""
+    rng = np.random.default_rng(seed)
+    cols, rows = [], []
+    bounds = np.concatenate([[0], np.cumsum(sizes)])
+    for f, size in enumerate(sizes):
+        cat = np.minimum((size * rng.random(n) ** 3).astype(np.int64), size - 1)
+        r = np.nonzero(rng.random(n) >= (missing if size else 2.0))[0]
+        cols.append(bounds[f] + cat[r])
+        rows.append(r)
+    cols, rows = np.concatenate(cols), np.concatenate(rows)
+    order = np.lexsort((rows, cols))
+    ptr = np.concatenate([[0], np.cumsum(np.bincount(cols, minlength=bounds[-1]))]).astype(np.int64)
+    val = (0.5 + rng.random(rows.size)).astype(np.float32) if weighted else np.ones(rows.size, dtype=np.float32)
+    return ptr, rows[order].astype(np.int32), val, bounds.tolist()
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("n,sizes", [(1, [1]), (7, [3, 1]), (2049, [300, 0, 17, 64]), (5003, [1, 255, 256, 40, 9]), (70_001, [66_000, 30])])
+def test_shared_vector_of_a_saved_model_from_the_row_maps(n, sizes, weighted):
+    ptr, idx, val, bounds = one_hot_columns(n, sizes, 5, 0.1, weighted)
+    d, rng = bounds[-1], np.random.default_rng(6)
+    s = snap.Solver("csc", n, d, ptr, idx, val, rng.standard_normal(n).astype(np.float32), "ridge", 1e-2, group_bounds=bounds)
+    for scale in (1.0, 1e-3):
+        x = (scale * rng.standard_normal(d)).astype(np.float32)
+        s.set_model(x)
+        want = np.zeros(n)
+        np.add.at(want, idx, val.astype(np.float64) * np.repeat(x.astype(np.float64), np.diff(ptr)))
+        np.testing.assert_allclose(s.shared(), want, rtol=1.2e-7, atol=1e-12)     # fp64 sums rounded once: half an ulp
+
+
+@pytest.mark.parametrize("d,n", [(1, 50), (700, 5000), (4096, 3000), (30_011, 9001)])      # around the 4096 table slots
+def test_shared_vector_of_a_dual_model_with_popular_features(d, n):
+    rng = np.random.default_rng(7)
+    ptr, idx, val = zipf_rows(rng.integers(0, min(d, 40) + 1, n), d, 8)
+    y = np.where(rng.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    s = snap.Solver("csr", n, d, ptr, idx, val, y, "hinge", 1e-2)
+    alpha = rng.random(n).astype(np.float32)
+    s.set_model(alpha)
+    want = np.zeros(d)
+    np.add.at(want, idx, val.astype(np.float64) * np.repeat((y * alpha).astype(np.float64), np.diff(ptr)))
+    np.testing.assert_allclose(s.shared(), want, rtol=1.2e-7, atol=1e-9)
