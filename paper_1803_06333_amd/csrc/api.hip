@@ -94,6 +94,7 @@ int leave_group_sweeps(snap_handle* h) {
 }
 
 static int check_status(snap_handle* h) {
+    if (h->status_clean) return SNAP_OK;             // (the round trip is a third of a small request)
     hipLaunchKernelGGL(k_publish_status, dim3(1), dim3(WAVE), 0, h->compute, h->status, h->red.host_mapped + 7);
     SNAP_HIP(hipGetLastError());
     SNAP_HIP(hipStreamSynchronize(h->compute));
@@ -107,6 +108,7 @@ static int check_status(snap_handle* h) {
                   "is invalid (scale the data, or create the handle with auto_groups off and without group_bounds)");
         return SNAP_ESTATE;
     }
+    h->status_clean = st == 0;
     return SNAP_OK;
 }
 
@@ -134,6 +136,7 @@ static void destroy(snap_handle* h) {
     (void)hipFree(h->item_start);
     (void)hipFree(h->ticket);
     (void)hipFree(h->status);
+    (void)hipFree(h->predict_flag);
     (void)hipFree(h->x_snap);
     (void)hipFree(h->v_snap);
     (void)hipFree(h->share_bounds);
@@ -209,6 +212,8 @@ static int build(snap_handle* h, const snap_matrix* A, const float* y) {
     SNAP_TRY(reducer_alloc(h->red));
     SNAP_HIP(hipMalloc(&h->status, sizeof(uint32_t)));
     SNAP_HIP(hipMalloc(&h->ticket, sizeof(uint32_t)));
+    SNAP_HIP(hipMalloc(&h->predict_flag, sizeof(uint32_t)));
+    SNAP_TRY(fill_zero(h->predict_flag, 4, h->compute));
     SNAP_TRY(fill_zero(h->status, 4, h->compute));
     SNAP_TRY(fill_zero(h->ticket, 4, h->compute));
 
@@ -567,6 +572,7 @@ int snap_epoch(snap_handle* h, uint64_t perm_seed) {
         return SNAP_EINVAL;
     }
     if (h->m == 0) return SNAP_OK;
+    h->status_clean = false;
     const bool prof = h->opt.profile != 0;
     // group sweeps of the ridge loss can run out of the range of their fixed-point sums: the state before
     // the epoch is kept so that the epoch can be done again by the asynchronous engine

@@ -118,6 +118,8 @@ struct snap_handle {
     int64_t* item_start = nullptr;    // [n_large+1] prefix sums of items in epoch order
     uint32_t* ticket = nullptr;       // work-item counter
     uint32_t* status = nullptr;       // device error flag
+    bool status_clean = false;        // read as 0 since the last launch of a kernel that can raise it
+    uint32_t* predict_flag = nullptr; // device word of predict's input check, 0 between calls
     int64_t max_large = 0;
     // dual forms: popular features whose updates are summed per wavefront (null: none), count of moved rows
     uint32_t* hot_tag = nullptr;

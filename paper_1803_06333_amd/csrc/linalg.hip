@@ -292,24 +292,17 @@ __device__ __forceinline__ double dot_term(float a, float vv, float yy) {
 
 template <int KIND>
 __device__ __forceinline__ double dot_range(const uint32_t* __restrict__ idx, const float* __restrict__ val,
-                                            int64_t s0, int64_t s1, int64_t dense_e0, const float* __restrict__ v,
+                                            int64_t s0, int64_t s1, const float* __restrict__ v,
                                             const float* __restrict__ y, int first, int stride) {
     double acc = 0.0;
     for (int64_t k = s0 + first; k < s1; k += stride) {
-        uint32_t r;
+        uint32_t r = idx[k];
         float yy = 0.0f;
-        if (idx) {
-            const uint32_t raw = idx[k];
-            if (KIND == K_PRIMAL_LOGISTIC) {
-                r = raw & ~LABEL_BIT;
-                yy = (raw & LABEL_BIT) ? -1.0f : 1.0f;
-            } else {
-                r = raw;
-                if (KIND == K_PRIMAL_RIDGE) yy = y[r];
-            }
-        } else {
-            r = (uint32_t)(dense_e0 + (k - s0));
-            if (KIND != K_DUAL) yy = y[r];
+        if (KIND == K_PRIMAL_LOGISTIC) {
+            yy = (r & LABEL_BIT) ? -1.0f : 1.0f;
+            r &= ~LABEL_BIT;
+        } else if (KIND == K_PRIMAL_RIDGE) {
+            yy = y[r];
         }
         acc += dot_term<KIND>(val[k], v[r], yy);
     }
@@ -327,7 +320,7 @@ k_dots_small(const int64_t* __restrict__ ptr, const uint32_t* __restrict__ idx, 
     const int64_t nwaves = (int64_t)gridDim.x * blockDim.x / WAVE;
     for (int64_t c = c0 + wave0; c < c1; c += nwaves) {
         if (cls[c]) continue;
-        double acc = dot_range<KIND>(idx, val, ptr[c] - nnz_base, ptr[c + 1] - nnz_base, 0, v, y, lane, WAVE);
+        double acc = dot_range<KIND>(idx, val, ptr[c] - nnz_base, ptr[c + 1] - nnz_base, v, y, lane, WAVE);
         acc = wave_sum_d(acc);
         if (lane == 0) gdot[c] = acc;
     }
@@ -338,8 +331,7 @@ k_dots_small(const int64_t* __restrict__ ptr, const uint32_t* __restrict__ idx, 
 template <int KIND>
 __global__ void __launch_bounds__(LTPB)
 k_dots_large_partial(const int64_t* __restrict__ ptr, const uint32_t* __restrict__ idx, const float* __restrict__ val,
-                     int64_t nnz_base, int64_t dense_len, const int64_t* __restrict__ large_list,
-                     const int64_t* __restrict__ seg_off, int64_t l0, int64_t l1,
+                     int64_t nnz_base, const int64_t* __restrict__ large_list, const int64_t* __restrict__ seg_off, int64_t l0, int64_t l1,
                      int64_t SEG, const float* __restrict__ v, const float* __restrict__ y, double* __restrict__ partial) {
     __shared__ double scratch[LTPB / WAVE];
     const int64_t s = seg_off[l0] + blockIdx.x;       // global segment number
@@ -351,12 +343,58 @@ k_dots_large_partial(const int64_t* __restrict__ ptr, const uint32_t* __restrict
     const int64_t c = large_list[lo];
     const int64_t seg = s - seg_off[lo];
     int64_t b0, len;
-    if (dense_len > 0) { b0 = c * dense_len; len = dense_len; }
-    else { b0 = ptr[c] - nnz_base; len = ptr[c + 1] - ptr[c]; }
+    b0 = ptr[c] - nnz_base;
+    len = ptr[c + 1] - ptr[c];
     const int64_t e0 = seg * SEG, e1 = min(len, e0 + SEG);
-    double acc = dot_range<KIND>(dense_len > 0 ? nullptr : idx, val, b0 + e0, b0 + e1, e0, v, y, threadIdx.x, LTPB);
+    double acc = dot_range<KIND>(idx, val, b0 + e0, b0 + e1, v, y, threadIdx.x, LTPB);
     acc = block_sum_d(acc, scratch);
     if (threadIdx.x == 0) partial[s] = acc;
+}
+
+// Dense data: the same partial sums, eight columns per workgroup, so that the factor of a row (loss' or v) is read and
+// evaluated once for eight elements, and the loads of a step are independent.  V = 4 consecutive rows per thread where
+// the columns start on 16 bytes.  400 000 x 2 000, ridge: 1 002 us with one column per workgroup (v and y
+// read for every element), 478 us = 6.7 TB/s of the matrix.
+template <int KIND>
+__device__ __forceinline__ double row_factor(float vv, float yy) { return dot_term<KIND>(1.0f, vv, yy); }
+
+template <int KIND, int V, int DOT_COLS>
+__global__ void __launch_bounds__(LTPB)
+k_dots_dense_partial(const float* __restrict__ A, int64_t len, int64_t m, int64_t nseg, int64_t SEG, const float* __restrict__ v,
+                     const float* __restrict__ y, double* __restrict__ partial) {
+    typedef float vec __attribute__((ext_vector_type(V)));
+    __shared__ double s_sum[LTPB / WAVE][DOT_COLS];
+    const int64_t c0 = (int64_t)blockIdx.x / nseg * DOT_COLS, seg = (int64_t)blockIdx.x % nseg;
+    const int64_t e0 = seg * SEG, e1 = min(len, e0 + SEG);
+    double acc[DOT_COLS] = {};
+    const float* col[DOT_COLS];
+#pragma unroll
+    for (int q = 0; q < DOT_COLS; ++q) col[q] = A + min(c0 + q, m - 1) * len;      // (past the end: the last column again, not stored)
+    for (int64_t e = e0 + V * threadIdx.x; e < e1; e += V * LTPB) {                 // (V = 4: e1 is a multiple of 4)
+        vec a[DOT_COLS];
+#pragma unroll
+        for (int q = 0; q < DOT_COLS; ++q) a[q] = __builtin_nontemporal_load(reinterpret_cast<const vec*>(col[q] + e));
+        const vec vv = *reinterpret_cast<const vec*>(v + e);
+        vec yy = vec(0.0f);
+        if (KIND != K_DUAL) yy = *reinterpret_cast<const vec*>(y + e);
+#pragma unroll
+        for (int t = 0; t < V; ++t) {
+            const double u = row_factor<KIND>(vv[t], yy[t]);
+#pragma unroll
+            for (int q = 0; q < DOT_COLS; ++q) acc[q] += (double)a[q][t] * u;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < DOT_COLS; ++q) {
+        acc[q] = wave_sum_d(acc[q]);
+        if ((threadIdx.x & (WAVE - 1)) == 0) s_sum[threadIdx.x / WAVE][q] = acc[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < DOT_COLS && c0 + threadIdx.x < m) {
+        double t = 0.0;
+        for (int w = 0; w < LTPB / WAVE; ++w) t += s_sum[w][threadIdx.x];
+        partial[(c0 + threadIdx.x) * nseg + seg] = t;      // (dense: every column is split, into nseg parts)
+    }
 }
 
 __global__ void k_dots_large_finish(const int64_t* __restrict__ large_list, const int64_t* __restrict__ seg_off,
@@ -381,8 +419,21 @@ static int coord_dots_chunk(snap_handle* h, int64_t chunk, const ChunkView& cv, 
     }
     if (ck.l1 > ck.l0) {
         const int64_t nseg = ck.n_items / 2;
-        hipLaunchKernelGGL((k_dots_large_partial<KIND>), dim3((unsigned)nseg), dim3(LTPB), 0, h->compute, cv.ptr,
-                           cv.idx, cv.val, cv.nnz_base, dense_len, h->large_list, h->large_seg_off, ck.l0, ck.l1,
+        if (h->dense) {
+            const int64_t per_col = (dense_len + h->seg - 1) / h->seg;
+            // (two columns per workgroup where eight leave compute units without one: 30 011 x 333 takes 27 us
+            // instead of 34)
+            const int cols = (h->m + 7) / 8 * per_col >= 1024 ? 8 : 2;
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3((unsigned)((h->m + cols - 1) / cols * per_col)), dim3(LTPB), 0, h->compute, cv.val,
+                                   dense_len, h->m, per_col, h->seg, h->v, h->y, h->seg_partial);
+            };
+            const bool wide = dense_len % 4 == 0 && h->seg % 4 == 0;
+            if (cols == 8) wide ? launch(k_dots_dense_partial<KIND, 4, 8>) : launch(k_dots_dense_partial<KIND, 1, 8>);
+            else wide ? launch(k_dots_dense_partial<KIND, 4, 2>) : launch(k_dots_dense_partial<KIND, 1, 2>);
+        } else
+            hipLaunchKernelGGL((k_dots_large_partial<KIND>), dim3((unsigned)nseg), dim3(LTPB), 0, h->compute, cv.ptr,
+                           cv.idx, cv.val, cv.nnz_base, h->large_list, h->large_seg_off, ck.l0, ck.l1,
                            h->seg, h->v, h->y, h->seg_partial);
         hipLaunchKernelGGL(k_dots_large_finish, dim3((unsigned)((ck.l1 - ck.l0 + 255) / 256)), dim3(256), 0,
                            h->compute, h->large_list, h->large_seg_off, ck.l0, ck.l1, h->seg_partial, h->gdot);
@@ -561,6 +612,7 @@ __global__ void k_scale(const float* __restrict__ in, float s, float* __restrict
 // the group sweeps, and the inner products are taken column by column instead.
 static int gradient_dots(snap_handle* h) {
     if (!h->grouped) return coord_dots(h);
+    h->status_clean = false;
     SNAP_TRY(grouped_dots(h));
     if (h->kind != K_PRIMAL_RIDGE) return SNAP_OK;
     uint32_t st = 0;
@@ -759,45 +811,104 @@ int access_moments(snap_handle* h, const uint32_t* freq, double* eff_len) {
 
 // ---- decision values -------------------------------------------------------------------------------
 // L lanes per row (8 ... 64, chosen from the average row length): with the 39 entries of a click-log
-// row a whole wavefront per row leaves a third of the lanes idle for one round of loads per row.
+// row a whole wavefront per row leaves a third of the lanes idle for one round of loads per row.  A row is a
+// chain of dependent loads (ptr, index, weight): the rounds of a row are asked for together (1 M rows of
+// 39 entries: 152 -> 141 us; 8 or 32 lanes 152 and 155; the non-temporal hint on the values 153, on both 164).  What
+// is left is the rate of the gathers, 280 G/s.
 template <int L>
 __global__ void __launch_bounds__(LTPB)
 k_csr_rowdot(const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx, const float* __restrict__ val,
              int64_t rows, const float* __restrict__ w, float* __restrict__ out) {
+    constexpr int ROUNDS = 4;
     const int sub = threadIdx.x & (L - 1);
     const int64_t g0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / L;
     const int64_t groups = (int64_t)gridDim.x * blockDim.x / L;
     for (int64_t i = g0; i < rows; i += groups) {
         double acc = 0.0;
         const int64_t s1 = ptr[i + 1];
-        for (int64_t k = ptr[i] + sub; k < s1; k += L) acc += (double)val[k] * (double)w[idx[k]];
+        for (int64_t k0 = ptr[i] + sub; k0 < s1; k0 += L * ROUNDS) {
+            int32_t e[ROUNDS];
+            float a[ROUNDS], ww[ROUNDS];
+#pragma unroll
+            for (int u = 0; u < ROUNDS; ++u) {
+                const int64_t k = k0 + u * L;
+                e[u] = k < s1 ? idx[k] : -1;
+                a[u] = k < s1 ? val[k] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < ROUNDS; ++u) ww[u] = e[u] >= 0 ? w[e[u]] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < ROUNDS; ++u) acc += (double)a[u] * (double)ww[u];
+        }
 #pragma unroll
         for (int off = L / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, L);   // the row's L lanes are all here
         if (sub == 0) out[i] = (float)acc;
     }
 }
 
-// dense: out[i] = sum_j X(i,j) w[j]; element (i,j) at X[i*rs + j*cs]
+// dense, row-major: out[i] = sum_j X[i*cols + j] w[j], one wavefront per row, ROUNDS independent loads of V consecutive
+// elements per lane (V = 4 where the rows start on 16 bytes).  1 023 rows of 2 000: 8.6 -> 3.9 us.
+template <int V>
 __global__ void __launch_bounds__(LTPB)
-k_dense_rowdot(const float* __restrict__ X, int64_t rows, int64_t cols, int64_t rs, int64_t cs,
-               const float* __restrict__ w, float* __restrict__ out) {
-    if (cs == 1) {      // row-major: one wavefront per row
-        const int lane = threadIdx.x & (WAVE - 1);
-        const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
-        const int64_t nwaves = (int64_t)gridDim.x * blockDim.x / WAVE;
-        for (int64_t i = wave0; i < rows; i += nwaves) {
-            double acc = 0.0;
-            for (int64_t j = lane; j < cols; j += WAVE) acc += (double)X[i * rs + j] * (double)w[j];
-            acc = wave_sum_d(acc);
-            if (lane == 0) out[i] = (float)acc;
+k_dense_rowdot(const float* __restrict__ X, int64_t rows, int64_t cols, const float* __restrict__ w, float* __restrict__ out) {
+    constexpr int ROUNDS = 4;
+    typedef float vec __attribute__((ext_vector_type(V)));
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
+    const int64_t nwaves = (int64_t)gridDim.x * blockDim.x / WAVE;
+    const int64_t packs = cols / V;                        // (V = 4: cols is a multiple of 4)
+    for (int64_t i = wave0; i < rows; i += nwaves) {
+        const vec* row = reinterpret_cast<const vec*>(X + i * cols);
+        const vec* wv = reinterpret_cast<const vec*>(w);
+        double acc = 0.0;
+        for (int64_t j0 = lane; j0 < packs; j0 += WAVE * ROUNDS) {
+            vec a[ROUNDS], b[ROUNDS];
+#pragma unroll
+            for (int u = 0; u < ROUNDS; ++u) {
+                const int64_t j = j0 + u * WAVE;
+                a[u] = j < packs ? row[j] : vec(0.0f);
+                b[u] = j < packs ? wv[j] : vec(0.0f);
+            }
+#pragma unroll
+            for (int u = 0; u < ROUNDS; ++u)
+#pragma unroll
+                for (int t = 0; t < V; ++t) acc += (double)a[u][t] * (double)b[u][t];
         }
-    } else {            // column-major: one thread per row, coalesced over rows
-        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < rows;
-             i += (int64_t)gridDim.x * blockDim.x) {
-            double acc = 0.0;
-            for (int64_t j = 0; j < cols; ++j) acc += (double)X[i + j * cs] * (double)w[j];
-            out[i] = (float)acc;
+        acc = wave_sum_d(acc);
+        if (lane == 0) out[i] = (float)acc;
+    }
+}
+
+// dense, column-major: element (i,j) at X[j*rows + i].  A workgroup takes 64 rows (one per lane) and splits
+// the columns over its 16 wavefronts, so that a few hundred rows still fill the loads' latency; the
+// wavefronts' sums are added in a fixed order.
+constexpr int COLDOT_WAVES = 16;
+__global__ void __launch_bounds__(WAVE * COLDOT_WAVES)
+k_dense_coldot(const float* __restrict__ X, int64_t rows, int64_t cols, const float* __restrict__ w, float* __restrict__ out) {
+    constexpr int ROUNDS = 8;
+    __shared__ double s_sum[COLDOT_WAVES][WAVE];
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
+    const int64_t i = (int64_t)blockIdx.x * WAVE + lane;
+    double acc = 0.0;
+    if (i < rows)
+        for (int64_t j0 = wave; j0 < cols; j0 += COLDOT_WAVES * ROUNDS) {
+            float a[ROUNDS], b[ROUNDS];
+#pragma unroll
+            for (int u = 0; u < ROUNDS; ++u) {
+                const int64_t j = j0 + u * COLDOT_WAVES;
+                a[u] = j < cols ? X[j * rows + i] : 0.0f;
+                b[u] = j < cols ? w[j] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < ROUNDS; ++u) acc += (double)a[u] * (double)b[u];
         }
+    s_sum[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0 && i < rows) {
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < COLDOT_WAVES; ++q) t += s_sum[q][lane];
+        out[i] = (float)t;
     }
 }
 
@@ -832,23 +943,31 @@ __global__ void k_check_compressed(const int64_t* __restrict__ ptr, const int32_
         const int64_t a = ptr[i];
         if (a < 0 || a > nnz || (i == 0 && a != 0) || (i == major && a != nnz) || (i < major && ptr[i + 1] < a)) bad = true;
     }
-    for (int64_t k = first; k < nnz; k += stride)
-        if (idx[k] < 0 || (int64_t)idx[k] >= minor) bad = true;
+    for (int64_t k0 = first; k0 < nnz; k0 += 4 * stride) {
+        int32_t e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) e[u] = k0 + u * stride < nnz ? idx[k0 + u * stride] : idx[k0];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) bad |= e[u] < 0 || (int64_t)e[u] >= minor;
+    }
     if (bad) atomicOr(flag, 1u);
 }
 
-// the flag of k_check_compressed reaches the host through mapped pinned memory, like the status word
-__global__ void k_publish_flag(const uint32_t* __restrict__ flag, double* __restrict__ host_mapped) {
-    if (threadIdx.x == 0) reinterpret_cast<uint32_t*>(host_mapped)[0] = *flag;
+// the flag of k_check_compressed reaches the host through mapped pinned memory, like the status word, and is
+// cleared for the next call
+__global__ void k_publish_flag(uint32_t* __restrict__ flag, double* __restrict__ host_mapped) {
+    if (threadIdx.x == 0) {
+        reinterpret_cast<uint32_t*>(host_mapped)[0] = *flag;
+        *flag = 0u;
+    }
 }
 
-// Checks ptr / idx of a compressed matrix in device memory; `flag` is one device word (cleared here).
+// Checks ptr / idx of a compressed matrix in device memory; `flag` is one device word, 0 between calls.
 static int check_compressed(snap_handle* h, int layout, const int64_t* dptr, const int32_t* didx, int64_t rows,
                             int64_t cols, int64_t count, uint32_t* flag) {
     const int64_t major = layout == SNAP_CSR ? rows : cols, minor = layout == SNAP_CSR ? cols : rows;
     const int64_t work = std::max<int64_t>(major + 1, count);
-    SNAP_TRY(fill_zero(flag, sizeof(uint32_t), h->compute));
-    hipLaunchKernelGGL(k_check_compressed, dim3((unsigned)std::min<int64_t>((work + 255) / 256, 16384)), dim3(256), 0,
+    hipLaunchKernelGGL(k_check_compressed, dim3((unsigned)std::min<int64_t>((work + 255) / 256, 4096)), dim3(256), 0,
                        h->compute, dptr, didx, major, minor, count, flag);
     hipLaunchKernelGGL(k_publish_flag, dim3(1), dim3(WAVE), 0, h->compute, flag, h->red.host_mapped + 6);
     SNAP_HIP(hipGetLastError());
@@ -889,9 +1008,12 @@ static int launch_rowdots(snap_handle* h, int layout, const int64_t* dptr, const
         hipLaunchKernelGGL(k_round_to_float, dim3((unsigned)(blocks < 16384 ? blocks : 16384)), dim3(256), 0, h->compute,
                            acc, dout, rows);
     } else if (layout == SNAP_DENSE_ROWMAJOR) {
-        hipLaunchKernelGGL(k_dense_rowdot, dim3(grid), dim3(LTPB), 0, h->compute, dval, rows, cols, cols, (int64_t)1, w, dout);
+        const bool wide = cols % 4 == 0 && ((uintptr_t)dval & 15) == 0 && ((uintptr_t)w & 15) == 0;
+        if (wide) hipLaunchKernelGGL((k_dense_rowdot<4>), dim3(grid), dim3(LTPB), 0, h->compute, dval, rows, cols, w, dout);
+        else hipLaunchKernelGGL((k_dense_rowdot<1>), dim3(grid), dim3(LTPB), 0, h->compute, dval, rows, cols, w, dout);
     } else {
-        hipLaunchKernelGGL(k_dense_rowdot, dim3(grid), dim3(LTPB), 0, h->compute, dval, rows, cols, (int64_t)1, rows, w, dout);
+        hipLaunchKernelGGL(k_dense_coldot, dim3((unsigned)((rows + WAVE - 1) / WAVE)), dim3(WAVE * COLDOT_WAVES), 0, h->compute, dval,
+                           rows, cols, w, dout);
     }
     SNAP_HIP(hipGetLastError());
     return SNAP_OK;
@@ -906,14 +1028,12 @@ int predict(snap_handle* h, const snap_matrix* X, float* out) {
     int32_t* didx = nullptr;
     float* dval = nullptr;
     float* dout = nullptr;
-    uint32_t* flag = nullptr;
     double* acc = nullptr;
     int rc = SNAP_OK;
     const bool sparse = X->layout == SNAP_CSR || X->layout == SNAP_CSC;
     const int64_t major = X->layout == SNAP_CSR ? rows : cols;
     const int64_t count = sparse ? X->nnz : rows * cols;
     auto cleanup = [&]() {
-        (void)hipFree(flag);
         (void)hipFree(acc);
         if (!on_dev) {
             (void)hipFree(dptr);
@@ -948,8 +1068,7 @@ int predict(snap_handle* h, const snap_matrix* X, float* out) {
         PRED_HIP(hipMalloc(&dout, (size_t)(rows ? rows : 1) * sizeof(float)));
     }
     if (sparse) {
-        PRED_HIP(hipMalloc(&flag, sizeof(uint32_t)));
-        rc = check_compressed(h, X->layout, dptr, didx, rows, cols, count, flag);
+        rc = check_compressed(h, X->layout, dptr, didx, rows, cols, count, h->predict_flag);
         if (rc != SNAP_OK) {
             cleanup();
             return rc;

@@ -116,3 +116,66 @@ def test_shared_vector_of_a_dual_model_with_popular_features(d, n):
     want = np.zeros(d)
     np.add.at(want, idx, val.astype(np.float64) * np.repeat((y * alpha).astype(np.float64), np.diff(ptr)))
     np.testing.assert_allclose(s.shared(), want, rtol=1.2e-7, atol=1e-9)
+
+
+def model_handle(w, loss="ridge"):
+    d = w.size
+    s = snap.Solver("csc", 4, d, np.arange(d + 1, dtype=np.int64), (np.arange(d) % 4).astype(np.int32), np.ones(d, dtype=np.float32),
+                    np.ones(4, dtype=np.float32), loss, 1e-3, auto_groups=False)
+    s.set_model(w)
+    return s
+
+
+@pytest.mark.parametrize("offset", [0, 1])                 # rows on 16 bytes, and not
+@pytest.mark.parametrize("rows,d", [(1, 1), (3, 255), (65, 256), (64, 1023), (130, 4096), (1000, 129)])
+def test_dense_requests_of_every_shape(rows, d, offset):
+    rng = np.random.default_rng(rows * d)
+    w, X = rng.standard_normal(d).astype(np.float32), rng.standard_normal((rows, d)).astype(np.float32)
+    s = model_handle(w)
+    want = X.astype(np.float64) @ w.astype(np.float64)
+    bound = 1.2e-7 * np.abs(want) + 1e-13 * (np.abs(X) @ np.abs(w).astype(np.float64))      # fp64 sums rounded once
+    for layout, flat in (("dense_rowmajor", X), ("dense_colmajor", X.T)):
+        buf = torch.empty(rows * d + offset, device=DEV)
+        buf[offset:] = torch.from_numpy(np.ascontiguousarray(flat).ravel())
+        got = s.predict(layout, rows, None, None, buf[offset:]).cpu().numpy()
+        assert (np.abs(got - want) <= bound).all()
+
+
+@pytest.mark.parametrize("top", [1, 17, 70, 150, 700])     # lanes per row 8, 8, 16 ... 64; rows shorter and longer than a step
+def test_sparse_rows_of_every_length_and_a_refused_matrix(top):
+    rng = np.random.default_rng(top)
+    rows, d = 501, 900
+    k = rng.integers(0, top + 1, rows)
+    k[-1] = 2 * top
+    ptr = np.concatenate([[0], np.cumsum(k)]).astype(np.int64)
+    idx, val = rng.integers(0, d, ptr[-1]).astype(np.int32), rng.standard_normal(ptr[-1]).astype(np.float32)
+    w = rng.standard_normal(d).astype(np.float32)
+    s = model_handle(w)
+    want = np.zeros(rows)
+    np.add.at(want, np.repeat(np.arange(rows), k), val.astype(np.float64) * w[idx])
+    for _ in range(2):
+        np.testing.assert_allclose(s.predict("csr", rows, ptr, idx, val), want, rtol=1.2e-7, atol=1e-9)
+        bad = idx.copy()
+        bad[-1] = d
+        with pytest.raises(snap.SnapError):
+            s.predict("csr", rows, ptr, bad, val)          # refused, and the next call is not
+
+
+@pytest.mark.parametrize("loss", ["ridge", "logistic"])
+@pytest.mark.parametrize("n,d", [(5, 1), (255, 9), (1024, 8), (16_384, 3), (16_388, 17), (33_001, 40), (20_000, 4200)])
+def test_duality_gap_of_dense_data_of_every_shape(n, d, loss):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + d)
+    A = torch.randn(d, n, generator=g, device=DEV)
+    y = torch.randn(n, generator=g, device=DEV)
+    if loss == "logistic":
+        y = torch.where(y >= 0, 1.0, -1.0)
+    w = torch.randn(d, generator=g, device=DEV) * 0.1 / d ** 0.5
+    lam = 1e-2
+    s = snap.Solver("dense_colmajor", n, d, None, None, A.view(-1), y, loss, lam)
+    s.set_model(w.cpu().numpy())
+    v = torch.from_numpy(s.shared()).to(DEV).double()
+    u = v - y.double() if loss == "ridge" else -y.double() * torch.sigmoid(-y.double() * v)
+    grad = torch.stack([torch.dot(A[j].double(), u) for j in range(d)]) / n + lam * w.double()
+    want = float(grad.square().sum()) / (2 * lam)
+    assert abs(s.duality_gap() - want) <= 1e-9 * want      # fp64 throughout: the order of the sums
