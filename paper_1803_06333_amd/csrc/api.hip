@@ -333,7 +333,7 @@ static int build(snap_handle* h, const snap_matrix* A, const float* y) {
     SNAP_TRY(fill_zero(h->v, (size_t)h->vlen * sizeof(float), h->compute));
     SNAP_TRY(fill_zero(h->perm, (size_t)m * sizeof(uint32_t), h->compute));
     SNAP_TRY(fill_zero(h->keys, (size_t)m * sizeof(uint32_t), h->compute));
-    SNAP_TRY(sorter_alloc(h->sorter, h->max_chunk_m));
+    SNAP_TRY(sorter_alloc(h->sorter, h->max_chunk_m, h->compute));
     if (h->opt.host_keys) SNAP_TRY(host_keys_alloc(h, h->max_chunk_m));
     SNAP_HIP(hipMalloc(&h->order, (size_t)(h->max_chunk_m ? h->max_chunk_m : 1) * sizeof(uint32_t)));
     SNAP_HIP(hipMalloc(&h->lstate, (size_t)(h->max_large + 1) * sizeof(LargeState)));

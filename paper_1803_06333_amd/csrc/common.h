@@ -58,11 +58,14 @@ struct ChunkView {
     int64_t c0, c1;
 };
 
-struct Sorter {              // scratch of the radix sort, sized for max_m coordinates
+struct Sorter {              // scratch of the sorts, sized for max_m coordinates
     uint32_t *keys_a = nullptr, *keys_b = nullptr, *vals_a = nullptr, *vals_b = nullptr;
     uint32_t* block_hist = nullptr;
     int64_t max_m = 0;
     int64_t n_blocks = 0;
+    uint64_t *bucket = nullptr, *bucket_list = nullptr;   // (key << 32 | index) by leading bits; elements that found their bucket full
+    uint32_t* bucket_counts = nullptr;                    // two sets of counters, used in turn
+    int bucket_slots = 0, bucket_flip = 0;
 };
 
 struct Reducer {             // scratch for deterministic fp64 reductions
@@ -253,7 +256,7 @@ struct snap_handle {
 namespace snap {
 
 // perm.hip
-int sorter_alloc(Sorter& s, int64_t max_m);
+int sorter_alloc(Sorter& s, int64_t max_m, hipStream_t stream);
 void sorter_free(Sorter& s);
 // keys_out[c] = key(seed, chunk, c) for c in [0, m); order_out = coordinates sorted by (key, c);
 // part_out = the same order stably partitioned by cls[c0 + c] (class 0 first); either may be null.

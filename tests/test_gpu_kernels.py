@@ -179,3 +179,38 @@ def test_duality_gap_of_dense_data_of_every_shape(n, d, loss):
     grad = torch.stack([torch.dot(A[j].double(), u) for j in range(d)]) / n + lam * w.double()
     want = float(grad.square().sum()) / (2 * lam)
     assert abs(s.duality_gap() - want) <= 1e-9 * want      # fp64 throughout: the order of the sums
+
+
+@pytest.mark.parametrize("slots", [256, 50, 1])           # buckets that hold everything, some of it, almost nothing
+@pytest.mark.parametrize("m", [1, 2, 127, 128, 129, 1000, 4097, 60_013, 262_145])
+def test_epoch_order_by_buckets(m, slots, monkeypatch):
+    if slots < 256:
+        monkeypatch.setenv("SNAP_SORT_SLOTS", str(slots))
+        m = min(m, 4097 if slots == 1 else 20_011)         # (the list of a full bucket is searched linearly)
+    n = 8
+    s = snap.Solver("csc", n, m, np.arange(m + 1, dtype=np.int64), (np.arange(m) % n).astype(np.int32), np.ones(m, dtype=np.float32),
+                    np.ones(n, dtype=np.float32), "ridge", 1.0, auto_groups=False)
+    for seed in (0, 1, 12345, 2 ** 63 + 5):
+        s.epoch(seed)
+        assert np.array_equal(s.perm(), oracle.permutation(seed, m))
+
+
+@pytest.mark.parametrize("host_keys", [False, True])
+def test_epoch_order_of_two_classes_and_of_more_coordinates_than_buckets_take(host_keys, monkeypatch):
+    monkeypatch.setenv("SNAP_SMALL_MAX", "2")
+    m, n = 5_003, 64
+    k = np.where(np.arange(m) % 3 == 0, 3, 1)
+    ptr = np.concatenate([[0], np.cumsum(k)]).astype(np.int64)
+    idx = np.concatenate([np.arange(q) * 7 for q in k]).astype(np.int32)
+    s = snap.Solver("csc", n, m, ptr, idx, np.ones(idx.size, dtype=np.float32), np.ones(n, dtype=np.float32), "ridge", 1.0,
+                    auto_groups=False, host_keys=host_keys)
+    for seed in (3, 4):
+        s.epoch(seed)
+        p = oracle.permutation(seed, m)
+        assert np.array_equal(s.perm(), np.concatenate([p[k[p] > 2], p[k[p] <= 2]]))
+    monkeypatch.delenv("SNAP_SMALL_MAX")
+    m = (1 << 21) + 1
+    s = snap.Solver("csc", 4, m, np.arange(m + 1, dtype=np.int64), (np.arange(m) % 4).astype(np.int32), np.ones(m, dtype=np.float32),
+                    np.ones(4, dtype=np.float32), "ridge", 1.0, auto_groups=False, host_keys=host_keys)
+    s.epoch(9)
+    assert np.array_equal(s.perm(), oracle.permutation(9, m))
