@@ -142,6 +142,7 @@ static void destroy(snap_handle* h) {
     (void)hipFree(h->share_bounds);
     (void)hipFree(h->share_out);
     hot_free(h);
+    (void)hipFree(h->step_prep);
     stream_free(h);
     dense_tiles_free(h);
     grouped_free(h);
@@ -448,6 +449,7 @@ static int build(snap_handle* h, const snap_matrix* A, const float* y) {
     if (h->grouped && h->kind == K_PRIMAL_RIDGE) SNAP_TRY(alloc_snapshots(h));     // (see snap_epoch: the range guard)
     if (use_tiles) SNAP_TRY(dense_tiles_setup(h));
     SNAP_TRY(hot_setup(h));
+    SNAP_TRY(lds_epoch_setup(h));
     if (h->form == SNAP_DUAL && h->loss == SNAP_LOGISTIC && m > 0) {
         // the entropy term of the logistic dual needs alpha inside (0,1): start at 1/2, v = A alpha
         SNAP_TRY(fill_value(h->x, 0.5f, m, h->compute));

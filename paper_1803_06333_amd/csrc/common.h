@@ -127,6 +127,7 @@ struct snap_handle {
     // dual forms: popular features whose updates are summed per wavefront (null: none), count of moved rows
     uint32_t* hot_tag = nullptr;
     uint32_t* moved = nullptr;
+    double* step_prep = nullptr;      // [m][2] epochs with v in LDS: the part of a coordinate's step that does not need v (null: not used)
 
     // chunks (resident: one chunk covering everything)
     struct Chunk { int64_t c0, c1, nnz0, nnz1, n_small, n_large, n_items, l0, l1; };   // [l0,l1): its range of large_list
@@ -267,6 +268,7 @@ int make_permutation(snap_handle* h, uint64_t seed, uint32_t chunk, int64_t c0, 
 
 // scd.hip
 int scd_run_chunk(snap_handle* h, const ChunkView& cv, const snap_handle::Chunk& ck, const uint32_t* order);
+int lds_epoch_setup(snap_handle* h); // epochs with v in LDS
 int hot_setup(snap_handle* h);       // popular features of the dual forms
 void hot_reset(snap_handle* h);      // the model is no longer the last epoch's
 void hot_free(snap_handle* h);

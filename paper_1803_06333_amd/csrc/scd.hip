@@ -227,7 +227,10 @@ struct MergeShape {
     __device__ static __forceinline__ int lane_of(int row) { return S == 32 ? (row >> 1) + 32 * (row & 1) : row; }
     // value of the row that register j of this lane belongs to, from the lanes that hold the rows' values
     __device__ static __forceinline__ int spread(int x, int j, bool upper) {
-        if (S == 32) return upper ? __builtin_amdgcn_readlane(x, 32 + j) : __builtin_amdgcn_readlane(x, j);
+        if (S == 32) {
+            const int a = __builtin_amdgcn_readlane(x, j), b = __builtin_amdgcn_readlane(x, 32 + j);
+            return upper ? b : a;
+        }
         return __builtin_amdgcn_readlane(x, j / PER_ROW);
     }
 };
@@ -261,12 +264,14 @@ __device__ __forceinline__ float sum_rows(const float (&p)[MergeShape<S, R>::REG
         const float t2 = fold_pair<QUAD_SWAP_1>(q[4], q[5], b0), t3 = fold_pair<QUAD_SWAP_1>(q[6], q[7], b0);
         const float u0 = fold_pair<QUAD_SWAP_2>(t0, t1, b1), u1 = fold_pair<QUAD_SWAP_2>(t2, t3, b1);
         x = fold_pair<ROW_ROR_4>(u0, u1, b2);              // (each part travels to one lane of the other kind)
+    } else if constexpr (NP == 1) {
+        return wave_sum(q[0]);
     } else if constexpr (NP == 2) {
         x = fold_pair<QUAD_SWAP_1>(q[0], q[1], b0);
         x += dpp_move<QUAD_SWAP_2>(x);
         x += dpp_move<ROW_ROR_4>(x);
     } else {
-        static_assert(NP == 4, "two, four or eight sums");
+        static_assert(NP == 4, "one, two, four or eight sums");
         const float t0 = fold_pair<QUAD_SWAP_1>(q[0], q[1], b0), t1 = fold_pair<QUAD_SWAP_1>(q[2], q[3], b0);
         x = fold_pair<QUAD_SWAP_2>(t0, t1, b1);
         x += dpp_move<ROW_ROR_4>(x);
@@ -536,12 +541,173 @@ int hot_setup(snap_handle* h) {
     return SNAP_OK;
 }
 
+// Creation: scratch of the epoch with v in LDS, where that may be used.
+int lds_epoch_setup(snap_handle* h) {
+    int lds_max = 0;
+    SNAP_HIP(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device));
+    if (h->dense || h->nnz_small < 1 || h->grouped || h->vlen < 1 || h->vlen * (int64_t)sizeof(double) > lds_max) return SNAP_OK;
+    SNAP_HIP(hipMalloc(&h->step_prep, (size_t)h->m * 2 * sizeof(double)));
+    return SNAP_OK;
+}
+
 void hot_reset(snap_handle* h) { reinterpret_cast<volatile uint32_t*>(h->red.host + MOVED_WORD)[0] = 0xFFFFFFFFu; }
 
 void hot_free(snap_handle* h) {
     (void)hipFree(h->hot_tag);
     (void)hipFree(h->moved);
     h->hot_tag = h->moved = nullptr;
+}
+
+// ---- short coordinates, short shared vector: v in the LDS of one compute unit ----------------------
+// With few coordinates in flight (the cap is a quarter of v's length) an epoch is a chain of visits, and a visit waits for
+// its gather and its atomics: 1.4 us for a column of 200 nonzeros (7.7 ns per scattered atomic of a compute unit), more
+// where the lines are contended.  A v of up to 20 000 entries fits the LDS of one compute unit as fp64, where 64
+// scattered additions take 20 cycles and 64 reads 6 (eight wavefronts; ds_add_f32 takes 192).  So one workgroup
+// runs the epoch: the other 255 compute units could not have shortened the chain.  v is rounded to fp32 once, at the end.
+//
+// What limits it is the issue rate of four SIMDs, then the wait for the nonzeros: R coordinates per visit share the
+// reduction and the step (as in k_scd_merge), the part of the step that does not need v is computed by a launch of its own
+// for all coordinates (k_prepare_steps: no coordinate is visited twice in an epoch), and nonzeros are requested two visits
+// ahead, in three slots that change roles by name (a register move would wait for the load).  No coordinate is longer than
+// its S places.  60 013 logistic rows of up to 23 nonzeros over 5 003 features, 88 in flight: 1.85 -> 0.95 ms per epoch (1.06 with
+// R = 4); 1 000 logistic columns of 200 nonzeros over 10 000 rows, 12 in flight: 118 -> 103 us, issue-bound: 180 vector
+// instructions per column.
+template <int KIND>
+__global__ void __launch_bounds__(256)
+k_prepare_steps(int64_t c0, int64_t c1, const float* __restrict__ x, const float* __restrict__ norms, const float* __restrict__ y,
+                StepParams sp, double2* __restrict__ prep) {
+    for (int64_t c = c0 + (int64_t)blockIdx.x * 256 + threadIdx.x; c < c1; c += (int64_t)gridDim.x * 256) {
+        const StepPrep p = prepare_step<KIND>(x[c], norms[c], KIND == K_DUAL ? y[c] : 0.0f, sp);
+        prep[c] = make_double2(p.a, p.b);
+    }
+}
+
+// most wavefronts of the workgroup (three slots of 16 registers of nonzeros leave room for eight)
+constexpr int lds_waves(int S) { return S == 1024 ? 8 : 16; }
+
+template <int KIND, int S, int R>
+__global__ void __launch_bounds__(WAVE * lds_waves(S))
+k_scd_lds(ChunkView cv, const uint32_t* __restrict__ order, int64_t n_small, const float* __restrict__ y, float* __restrict__ x,
+          float* __restrict__ v, int64_t vlen, const float* __restrict__ norms, const double2* __restrict__ prep, StepParams sp) {
+    using Shape = MergeShape<S, R>;
+    constexpr int ROWS = R, REGS = Shape::REGS, PER_ROW = Shape::PER_ROW;
+    constexpr uint32_t IDX_MASK = KIND == K_PRIMAL_LOGISTIC ? ~LABEL_BIT : 0xFFFFFFFFu;
+    extern __shared__ double s_shared[];
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int64_t n_waves = blockDim.x / WAVE, wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const bool upper = lane >= 32;
+    const int row = Shape::row_of(lane);
+    const bool owner = lane == Shape::lane_of(row);
+    // (ridge: v - y, all that the steps need of the two)
+    for (int64_t i = threadIdx.x; i < vlen; i += blockDim.x) s_shared[i] = (double)v[i] - (KIND == K_PRIMAL_RIDGE ? (double)y[i] : 0.0);
+    __syncthreads();
+
+    // Every lane loads, from a valid place: what does not belong to it is masked where it is used, and no branch keeps a
+    // load and its wait together.  The empty asm statements hold the arithmetic on a loaded value back to the visit
+    // that uses it (the compiler would convert it right behind the load, and wait there).
+    struct Rows {
+        int64_t c, s0;                // this lane's coordinate, its first nonzero in the chunk's arrays
+        int len;
+        uint32_t raw[REGS];
+        float a[REGS];
+        float xc, nc, yc;
+        double2 pr;
+    };
+    struct Range { int64_t c, p0, p1; };
+    auto load_entry = [&](int64_t g) -> uint32_t { return order[min(g * ROWS + row, n_small - 1)]; };
+    auto load_range = [&](int64_t g, uint32_t entry) -> Range {
+        const int64_t c = cv.c0 + (int64_t)entry;
+        return Range{g * ROWS + row < n_small ? c : -1, cv.ptr[c], cv.ptr[c + 1]};
+    };
+    auto place = [&](int j) -> int { return S == 32 ? (lane & 31) : (j % PER_ROW) * WAVE + lane; };
+    auto fetch = [&](Rows& q, const Range& r) {
+        const int64_t c = r.c >= 0 ? r.c : cv.c0;
+        q.c = r.c, q.s0 = r.p0 - cv.nnz_base, q.len = r.c >= 0 ? (int)(r.p1 - r.p0) : 0;
+        q.xc = x[c];
+        q.nc = q.yc = 0.0f;
+        q.pr = make_double2(0.0, 0.0);
+        if (KIND != K_PRIMAL_LOGISTIC) q.pr = prep[c];
+        if (KIND == K_DUAL) {
+            q.nc = norms[c];
+            q.yc = y[c];
+        }
+#pragma unroll
+        for (int j = 0; j < REGS; ++j) {
+            const uint32_t lo = (uint32_t)Shape::spread((int)(uint32_t)q.s0, j, upper);
+            const int hi = Shape::spread((int)(q.s0 >> 32), j, upper);
+            const int64_t k = (int64_t)(((uint64_t)(uint32_t)hi << 32) | lo) + place(j);
+            const int64_t at = place(j) < Shape::spread(q.len, j, upper) ? k : 0;
+            q.raw[j] = cv.idx[at];
+            q.a[j] = cv.val[at];
+        }
+    };
+    const int64_t n_visits = (n_small + ROWS - 1) / ROWS;
+    // visit g: the order entry of visit g + 4, the range of visit g + 3 and the nonzeros of visit g + 2 are requested, in
+    // this order, so that a wait for one of the first two is no wait for the nonzeros behind it
+    auto visit = [&](int64_t g, Rows& cur, Rows& nxt2, Range& range3, Range& range2, uint32_t& entry4, uint32_t& entry3) {
+        asm volatile("" : "+v"(entry3), "+v"(range2.p0), "+v"(range2.p1), "+v"(cur.xc), "+v"(cur.nc), "+v"(cur.yc), "+v"(cur.pr.x), "+v"(cur.pr.y));
+#pragma unroll
+        for (int j = 0; j < REGS; ++j) asm volatile("" : "+v"(cur.raw[j]), "+v"(cur.a[j]));
+        __builtin_amdgcn_sched_barrier(0);
+        float yy[REGS];
+        bool have[REGS];
+        double vv[REGS];
+#pragma unroll
+        for (int j = 0; j < REGS; ++j) {
+            have[j] = place(j) < Shape::spread(cur.len, j, upper);
+            yy[j] = 0.0f;
+            if (KIND == K_PRIMAL_LOGISTIC) yy[j] = (cur.raw[j] & LABEL_BIT) ? -1.0f : 1.0f;
+            vv[j] = s_shared[cur.raw[j] & IDX_MASK];
+        }
+        entry4 = load_entry(g + 4 * n_waves);
+        range3 = load_range(g + 3 * n_waves, entry3);
+        fetch(nxt2, range2);
+        __builtin_amdgcn_sched_barrier(0);
+        float pg[REGS], ph[REGS];
+#pragma unroll
+        for (int j = 0; j < REGS; ++j) {
+            pg[j] = ph[j] = 0.0f;
+            if (have[j]) accumulate<KIND>(cur.a[j], (float)vv[j], yy[j], pg[j], ph[j]);
+        }
+        float gs = sum_rows<S, R>(pg, lane), hs = 0.0f;
+        if (KIND == K_PRIMAL_LOGISTIC) hs = sum_rows<S, R>(ph, lane);
+        StepPrep p{cur.pr.x, cur.pr.y, 0.0};
+        if (KIND == K_DUAL) p.c = (double)cur.yc * sp.inv_lam_n;
+        float mult;
+        const float xn = finish_step<KIND>((double)gs, (double)hs, cur.xc, cur.nc, cur.yc, p, sp, mult);
+        if (cur.c < 0) mult = 0.0f;
+        if (owner && cur.c >= 0) x[cur.c] = xn;
+        if (__ballot(mult != 0.0f) != 0) {
+#pragma unroll
+            for (int j = 0; j < REGS; ++j) {
+                const float mj = __int_as_float(Shape::spread(__float_as_int(mult), j, upper));
+                if (have[j] && mj != 0.0f) unsafeAtomicAdd(&s_shared[cur.raw[j] & IDX_MASK], (double)(mj * cur.a[j]));
+            }
+        }
+    };
+    Rows q0, q1, q2;
+    Range r0, r1, r2;
+    uint32_t e0, e1, e2;
+    e0 = load_entry(wave0);
+    e1 = load_entry(wave0 + n_waves);
+    e2 = load_entry(wave0 + 2 * n_waves);
+    r0 = load_range(wave0, e0);
+    r1 = load_range(wave0 + n_waves, e1);
+    r2 = load_range(wave0 + 2 * n_waves, e2);
+    e0 = load_entry(wave0 + 3 * n_waves);
+    fetch(q0, r0);
+    fetch(q1, r1);
+    for (int64_t g = wave0; g < n_visits;) {
+        visit(g, q0, q2, r0, r2, e1, e0);
+        if ((g += n_waves) >= n_visits) break;
+        visit(g, q1, q0, r1, r0, e2, e1);
+        if ((g += n_waves) >= n_visits) break;
+        visit(g, q2, q1, r2, r1, e0, e2);
+        g += n_waves;
+    }
+    __syncthreads();
+    for (int64_t i = threadIdx.x; i < vlen; i += blockDim.x)
+        v[i] = (float)(s_shared[i] + (KIND == K_PRIMAL_RIDGE ? (double)y[i] : 0.0));
 }
 
 // ---- large coordinates: segments, two phases, ticket order -------------------------------------
@@ -780,6 +946,28 @@ static int launch_kind(snap_handle* h, const ChunkView& cv, const snap_handle::C
         int64_t waves = std::min<int64_t>(ck.n_small, 256 * 32);
         if (h->inflight_nnz > 0)
             waves = std::min<int64_t>(waves, std::max<int64_t>(1, (int64_t)((double)h->inflight_nnz / h->avg_small_len)));
+        // v in LDS where it fits and the chain of visits, not the work, takes the time.  Dual forms: below the 96 rows in
+        // flight from which several rows per wavefront pay (15.8 ns per row of up to 32 nonzeros against 31 ns with single rows, of
+        // which the contended lines are the larger part).  Primal forms, whose lines are not contended: a column of 200
+        // nonzeros takes 0.10 us of the one compute unit and 1.4 us / (columns in flight) otherwise: equal at 14.  Longer
+        // columns (up to 1 024) shift both sides alike.
+        const int64_t few = KIND == K_DUAL ? 95 : 14;
+        if (h->step_prep && waves <= few && h->max_small_len <= 1024) {
+            if (KIND != K_PRIMAL_LOGISTIC)
+                hipLaunchKernelGGL((k_prepare_steps<KIND>), dim3((unsigned)std::min<int64_t>((cv.c1 - cv.c0 + 255) / 256, 1024)), dim3(256), 0,
+                                   h->compute, cv.c0, cv.c1, h->x, h->norms, h->y, sp, (double2*)h->step_prep);
+            auto launch = [&](auto kernel, int most, int rows) {
+                const int64_t w = std::max<int64_t>(1, std::min<int64_t>(most, waves / rows));
+                hipLaunchKernelGGL(kernel, dim3(1), dim3((unsigned)(WAVE * w)), (size_t)h->vlen * sizeof(double), h->compute, cv, order,
+                                   ck.n_small, h->y, h->x, h->v, h->vlen, h->norms, (const double2*)h->step_prep, sp);
+            };
+            if (h->max_small_len <= 32 && waves >= 8) launch(k_scd_lds<KIND, 32, 8>, lds_waves(32), 8);
+            else if (h->max_small_len <= 64 && waves >= 4) launch(k_scd_lds<KIND, 64, 4>, lds_waves(64), 4);
+            else if (h->max_small_len <= 256) launch(k_scd_lds<KIND, 256, 1>, lds_waves(256), 1);
+            else launch(k_scd_lds<KIND, 1024, 1>, lds_waves(1024), 1);
+            SNAP_HIP(hipGetLastError());
+            return SNAP_OK;
+        }
         if constexpr (KIND == K_DUAL) {
             // Several rows per wavefront where popular features are contended for: eight while at least half of the
             // rows move (by the count of the last epoch that kept one; 0xFFFFFFFF: none yet), four down to one row in 32,

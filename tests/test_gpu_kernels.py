@@ -214,3 +214,60 @@ def test_epoch_order_of_two_classes_and_of_more_coordinates_than_buckets_take(ho
                     np.ones(4, dtype=np.float32), "ridge", 1.0, auto_groups=False, host_keys=host_keys)
     s.epoch(9)
     assert np.array_equal(s.perm(), oracle.permutation(9, m))
+
+
+@pytest.mark.parametrize("loss", ["ridge", "logistic", "elastic"])
+@pytest.mark.parametrize("n,d,top", [(300, 40, 32), (300, 40, 64), (900, 257, 250), (20_000, 64, 1024), (4_000, 30, 1025), (20_480, 33, 90), (20_481, 33, 90)])
+@pytest.mark.parametrize("in_flight", [1, 12])             # coordinates; one: exactly the sequential epoch
+def test_primal_epoch_with_the_shared_vector_in_lds(n, d, top, loss, in_flight):
+    rng = np.random.default_rng(n + top)
+    k = rng.integers(0, min(n, top) + 1, d)
+    k[0], k[-1] = min(n, top), 0
+    ptr = np.concatenate([[0], np.cumsum(k)]).astype(np.int64)
+    idx = np.concatenate([np.sort(rng.choice(n, q, replace=False)) for q in k]).astype(np.int32)
+    val = rng.standard_normal(idx.size).astype(np.float32)
+    name = "ridge" if loss == "elastic" else loss
+    y = rng.standard_normal(n).astype(np.float32)
+    if loss == "logistic":
+        y = np.where(y >= 0, 1.0, -1.0).astype(np.float32)
+    lam1 = 1e-3 if loss == "elastic" else 0.0
+    s = snap.Solver("csc", n, d, ptr, idx, val, y, name, 1e-2, lam1=lam1, auto_groups=False, adaptive=False,
+                    max_inflight_nnz=1 if in_flight == 1 else int(in_flight * max(1.0, idx.size / d)))
+    o = oracle.Solver(oracle.Matrix("csc", n, d, ptr, idx, val), y, name, 1e-2, lam1=lam1)
+    for e in range(12):
+        s.epoch(e)
+        o.epoch(e)
+        x = s.model()[1].astype(np.float64)
+        want = np.zeros(n)
+        np.add.at(want, idx, val.astype(np.float64) * np.repeat(x, k))
+        assert np.linalg.norm(s.shared() - want) <= 1e-5 * max(np.linalg.norm(want), 1e-6)
+        if in_flight == 1:                                 # fp32 steps against the fp64 oracle's, the same order
+            assert np.linalg.norm(x - o.x) <= 1e-4 * max(np.linalg.norm(o.x), 1e-6)
+    P, Po = s.objective(), o.primal()
+    assert abs(P - Po) <= 1e-4 * abs(Po)
+
+
+@pytest.mark.parametrize("loss", ["hinge", "logistic"])
+@pytest.mark.parametrize("top,d", [(1, 40), (32, 700), (33, 700), (64, 5_000), (65, 20_480), (256, 20_480), (300, 3_000), (40, 20_481)])
+@pytest.mark.parametrize("in_flight", [1, 20, 90])
+def test_dual_epoch_with_the_shared_vector_in_lds(top, d, loss, in_flight):
+    n = 403
+    lam = 60.0 / n
+    rng = np.random.default_rng(top)
+    k = rng.integers(0, top + 1, n)
+    k[3] = top
+    ptr, idx, val = zipf_rows(k, d, 14)
+    y = np.where(rng.random(n) < 0.5, 1.0, -1.0).astype(np.float32)
+    s = snap.Solver("csr", n, d, ptr, idx, val, y, loss, lam, max_inflight_nnz=1 if in_flight == 1 else int(in_flight * max(1.0, idx.size / n)))
+    o = oracle.Solver(oracle.Matrix("csr", n, d, ptr, idx, val), y, loss, lam)
+    for e in range(30):
+        s.epoch(e)
+        o.epoch(e)
+        if e < 3:
+            alpha = s.model()[1].astype(np.float64)
+            want = np.zeros(d)
+            np.add.at(want, idx, val.astype(np.float64) * np.repeat(y * alpha, np.diff(ptr)))
+            assert np.linalg.norm(s.shared() - want) <= 1e-5 * np.linalg.norm(want)
+            if in_flight == 1:
+                assert np.linalg.norm(alpha - o.x) <= 1e-4 * np.linalg.norm(o.x)
+    assert abs(s.objective(want_dual=True)[1] - o.dual()) <= 1e-4 * abs(o.dual())
