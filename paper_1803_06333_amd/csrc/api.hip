@@ -210,7 +210,7 @@ static int build(snap_handle* h, const snap_matrix* A, const float* y) {
     // hold up the sweep of the chunk they belong to
     if (h->opt.host_keys) SNAP_TRY(library_stream(h->device, 2, &h->hk_stream));
     for (auto& e : h->ev) SNAP_HIP(hipEventCreate(&e));
-    SNAP_TRY(reducer_alloc(h->red));
+    SNAP_TRY(reducer_alloc(h->red, h->compute));
     SNAP_HIP(hipMalloc(&h->status, sizeof(uint32_t)));
     SNAP_HIP(hipMalloc(&h->ticket, sizeof(uint32_t)));
     SNAP_HIP(hipMalloc(&h->predict_flag, sizeof(uint32_t)));

@@ -69,7 +69,8 @@ struct Sorter {              // scratch of the sorts, sized for max_m coordinate
 };
 
 struct Reducer {             // scratch for deterministic fp64 reductions
-    double* partial = nullptr;   // [REDUCE_BLOCKS * 4]
+    double* partial = nullptr;   // [sums of a launch][REDUCE_BLOCKS]
+    uint32_t* arrived = nullptr; // workgroups of a launch that are done, 0 between launches
     double* result = nullptr;    // [8] device
     double* host = nullptr;      // [9] pinned host, mapped into the device's address space
     double* host_mapped = nullptr;   // the device's pointer to the same memory
@@ -322,7 +323,7 @@ int chunk_gap_shares(snap_handle* h, double* shares_out);   // host array, one e
 int predict(snap_handle* h, const snap_matrix* X, float* out);
 int predict_static(snap_handle* h, const snap_matrix* X, float* out);   // no allocation: scratch in a static device array
 int weights_to_host(snap_handle* h, float* w_out);
-int reducer_alloc(Reducer& r);
+int reducer_alloc(Reducer& r, hipStream_t stream);
 void reducer_free(Reducer& r);
 int fill_zero(void* p, size_t bytes, hipStream_t s);
 // d0[0..n0) = s0, d1[0..n1) = s1 in one launch (arrays from hipMalloc)
