@@ -112,8 +112,10 @@ k_tile_pass(const float* __restrict__ A, int64_t ld, int64_t n, int64_t prev_c0,
         load_rows<ALIGNED, PASS_VEC>(v, i0, live, acc);
         if (n_prev > 0) {
             const float* col = A + prev_c0 * ld;
+            // (last column first: what the pass before read last may still be in the memory-side cache; 400 000 rows:
+            // 62.9 -> 61.0 us per pass.  The non-temporal hint on these loads takes 72 us, on all 114.)
 #pragma unroll 16
-            for (int j = 0; j < n_prev; ++j) {
+            for (int j = n_prev - 1; j >= 0; --j) {
                 float a[PASS_VEC];
                 load_rows<ALIGNED, PASS_VEC>(col + (int64_t)j * ld, i0, live, a);
                 const float mj = mult_s[j];
