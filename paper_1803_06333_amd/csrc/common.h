@@ -171,7 +171,7 @@ struct snap_handle {
     int* ghot_host = nullptr;         // [n_groups] number of hot (LDS-accumulated) ranks per group
     int* gk64_host = nullptr;         // [n_groups] of those, the leading ranks that keep two 64-bit sums (the rest: one packed word)
     bool gpack = false;               // packed ranks in use (logistic loss)
-    int g_row_wgs = 0, g_kd_max = 0;  // workgroups of a row pass; steps of the previous group kept in LDS
+    int g_row_wgs = 0, g_row_tpb = 1024, g_kd_max = 0;  // workgroups of a row pass and their threads; steps of the previous group kept in LDS
     void* rowmap = nullptr;           // [n_groups][n_pad]: rank of the row's coordinate in the group (uint16 or uint32)
     bool map16 = true;
     uint8_t* rowmap8 = nullptr;       // resident 16-bit maps: byte copies of the maps of groups with at most 255 coordinates

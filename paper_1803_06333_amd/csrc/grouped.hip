@@ -65,7 +65,7 @@ constexpr int HOT_DEFAULT = 12288;
 constexpr int HOT_MIN_ROWS = 32;                 // a rank is worth an LDS slot while its coordinate has that many rows
 constexpr int DELTA_LDS = 16384;                 // most steps of the previous group kept in LDS (tuning knob's ceiling)
 constexpr int DELTA_DEFAULT = 12288;
-constexpr int ROW_TPB = 1024;
+constexpr int ROW_TPB = 1024;                    // most threads of a row pass's workgroup (row_shape)
 constexpr int COLD_RING = 128;                   // entries per wavefront staged in LDS on their way to the short coordinates' buffer
 constexpr int ROW_WGS_DEFAULT = 256;             // one workgroup per compute unit
 constexpr int PACK_COUNT_MAX = 4095;             // rows of a coordinate whose two sums share one word
@@ -760,6 +760,21 @@ static bool resolution_too_coarse(const snap_handle* h, int scale_exp) {
     return h->kind == K_PRIMAL_LOGISTIC && h->lambda * (double)h->n < ldexp(1.0, 2 * scale_exp - 6);
 }
 
+// Launch shape of the row passes.  Every thread takes packs of eight (32-bit maps: four) rows one after the other, some 400
+// vector instructions each, so rows that do not fill the device are spread over as many compute units as
+// possible, in workgroups of down to 256 threads, and no workgroup is launched without rows (it would write an empty
+// part of the sums for the step kernel to read).  Row pass and step kernel with 256 workgroups of 1024 and this way: 40 009 rows 6.7 +
+// 3.5 and 5.1 + 3.2 us, 1 000 003 rows (two categorical fields) 10.4 + 5.5 and 10.2 + 4.6 us.
+static void row_shape(snap_handle* h, const int64_t* gb, int64_t G) {
+    int64_t most = 0;
+    for (int64_t g = 0; g < G; ++g) most = std::max(most, gb[g + 1] - gb[g]);
+    const int64_t R = most > 65535 ? 4 : 8, packs = (h->n + R - 1) / R, slots = (int64_t)wgs_per_cu() * ROW_WGS_DEFAULT;
+    h->g_row_tpb = ROW_TPB;
+    while (h->g_row_tpb > 256 && packs <= slots * (h->g_row_tpb / 2)) h->g_row_tpb /= 2;
+    h->g_row_wgs = (int)std::min<int64_t>(slots, std::max<int64_t>(1, (packs + h->g_row_tpb - 1) / h->g_row_tpb));
+    if (row_wgs_knob() > 0) h->g_row_wgs = row_wgs_knob();
+}
+
 int grouped_setup(snap_handle* h, const int64_t* hptr, const int64_t* gb, int64_t G) {
     const int64_t m = h->m, n = h->n;
     if (h->form != SNAP_PRIMAL || h->dense) {
@@ -792,7 +807,7 @@ int grouped_setup(snap_handle* h, const int64_t* hptr, const int64_t* gb, int64_
     h->gpack = pack_knob();
     h->g_kd_max = DELTA_DEFAULT / wgs_per_cu();
     if (const char* e = getenv("SNAP_DELTA_LDS")) h->g_kd_max = std::max(1, std::min(DELTA_LDS, atoi(e)));   // tuning knob
-    h->g_row_wgs = row_wgs_knob() > 0 ? row_wgs_knob() : wgs_per_cu() * ROW_WGS_DEFAULT;
+    row_shape(h, gb, G);
     const int hot_cap = hot_max(), min_rows = hot_min_rows();
     const int ring_bytes = compact_knob() ? (ROW_TPB / WAVE) * COLD_RING * (int)sizeof(float) : 0;
     const int lds_budget = lds_max / wgs_per_cu() - 1024 - 4 * h->g_kd_max - ring_bytes;   // bytes for the sums
@@ -1029,10 +1044,10 @@ __global__ void __launch_bounds__(ROW_TPB)
 k_cold_rows(const MAPT* __restrict__ map, int hot, int64_t n, uint32_t* __restrict__ slots, uint32_t* __restrict__ rowpos) {
     constexpr int R = MapTraits<MAPT>::R;
     constexpr uint32_t NONE = MapTraits<MAPT>::NONE;
-    const int wave = (int)blockIdx.x * (ROW_TPB / WAVE) + (int)threadIdx.x / WAVE;
+    const int wave = (int)blockIdx.x * (int)(blockDim.x / WAVE) + (int)threadIdx.x / WAVE;
     uint32_t run = WRITE ? slots[wave] : 0u;
     const int64_t packs = (n + R - 1) / R;                     // (the same walk over the rows as in the row pass)
-    for (int64_t q = (int64_t)blockIdx.x * ROW_TPB + threadIdx.x; q < packs; q += (int64_t)gridDim.x * ROW_TPB) {
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < packs; q += (int64_t)gridDim.x * blockDim.x) {
         uint32_t mc[R];
         unpack_ranks(map, load_map(map + R * q), mc);
 #pragma unroll
@@ -1067,7 +1082,7 @@ k_cold_index(const int64_t* __restrict__ ptr, const uint32_t* __restrict__ idx, 
 template <typename MAPT>
 static int cold_setup_maps(snap_handle* h, const std::vector<int64_t>& cold_rows, const std::vector<int64_t>& cptr, int64_t total) {
     const int64_t G = h->n_groups, m = h->m, n = h->n;
-    const int nwaves = h->g_row_wgs * (ROW_TPB / WAVE);
+    const int nwaves = h->g_row_wgs * (h->g_row_tpb / WAVE);
     const MAPT* maps = (const MAPT*)h->rowmap;
     const int64_t most = *std::max_element(cold_rows.begin(), cold_rows.end());
     uint32_t* rowpos = nullptr;
@@ -1091,7 +1106,7 @@ static int cold_setup_maps(snap_handle* h, const std::vector<int64_t>& cold_rows
     if (rc != SNAP_OK) return fail(rc);
     for (int64_t g = 0; g < G; ++g)
         if (h->gcompact_host[g])
-            hipLaunchKernelGGL((k_cold_rows<MAPT, false>), dim3((unsigned)h->g_row_wgs), dim3(ROW_TPB), 0, h->compute,
+            hipLaunchKernelGGL((k_cold_rows<MAPT, false>), dim3((unsigned)h->g_row_wgs), dim3(h->g_row_tpb), 0, h->compute,
                                maps + (size_t)g * h->n_pad, h->ghot_host[g], n, h->gwbase + (size_t)g * nwaves, (uint32_t*)nullptr);
     C_HIP(hipGetLastError());
     std::vector<uint32_t> slots((size_t)G * (size_t)nwaves);
@@ -1117,7 +1132,7 @@ static int cold_setup_maps(snap_handle* h, const std::vector<int64_t>& cold_rows
         if (!h->gcompact_host[g]) continue;
         const int64_t g0 = h->gbounds_host[g], sz = h->gbounds_host[g + 1] - g0;
         const int hot = h->ghot_host[g];
-        hipLaunchKernelGGL((k_cold_rows<MAPT, true>), dim3((unsigned)h->g_row_wgs), dim3(ROW_TPB), 0, h->compute,
+        hipLaunchKernelGGL((k_cold_rows<MAPT, true>), dim3((unsigned)h->g_row_wgs), dim3(h->g_row_tpb), 0, h->compute,
                            maps + (size_t)g * h->n_pad, hot, n, h->gwbase + (size_t)g * nwaves, rowpos);
         const int blocks = (int)std::min<int64_t>((sz - hot + 3) / 4, 16384);
         hipLaunchKernelGGL(k_cold_index, dim3((unsigned)blocks), dim3(256), 0, h->compute, h->ptr, h->idx, (int64_t)0, h->coord_of,
@@ -1198,7 +1213,7 @@ k_build_rowmap_group(const int64_t* __restrict__ ptr, const uint32_t* __restrict
 template <typename MAPT>
 static int streamed_setup_maps(snap_handle* h, const int64_t* hptr) {
     const int64_t G = h->n_groups, m = h->m, n = h->n;
-    const int nwaves = h->g_row_wgs * (ROW_TPB / WAVE);
+    const int nwaves = h->g_row_wgs * (h->g_row_tpb / WAVE);
     // host-side plan of the short coordinates' index lists (as for resident data)
     h->gcompact_host = new (std::nothrow) uint8_t[(size_t)G]();
     if (!h->gcompact_host) return SNAP_ENOMEM;
@@ -1430,7 +1445,7 @@ static int streamed_setup_maps(snap_handle* h, const int64_t* hptr) {
         }
         if (h->gcompact_host[g] && n > 0) {
             uint32_t* wb = h->gwbase + (size_t)g * nwaves;
-            hipLaunchKernelGGL((k_cold_rows<MAPT, false>), dim3((unsigned)h->g_row_wgs), dim3(ROW_TPB), 0, h->compute, dev_map,
+            hipLaunchKernelGGL((k_cold_rows<MAPT, false>), dim3((unsigned)h->g_row_wgs), dim3(h->g_row_tpb), 0, h->compute, dev_map,
                                hot, n, wb, (uint32_t*)nullptr);
             S_HIP(hipGetLastError());
             S_HIP(hipMemcpyAsync(slots.data(), wb, slots.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, h->compute));
@@ -1446,7 +1461,7 @@ static int streamed_setup_maps(snap_handle* h, const int64_t* hptr) {
                 return fail(SNAP_ESTATE);
             }
             S_HIP(hipMemcpyAsync(wb, slots.data(), slots.size() * sizeof(uint32_t), hipMemcpyHostToDevice, h->compute));
-            hipLaunchKernelGGL((k_cold_rows<MAPT, true>), dim3((unsigned)h->g_row_wgs), dim3(ROW_TPB), 0, h->compute, dev_map,
+            hipLaunchKernelGGL((k_cold_rows<MAPT, true>), dim3((unsigned)h->g_row_wgs), dim3(h->g_row_tpb), 0, h->compute, dev_map,
                                hot, n, wb, rowpos);
             const int blocks = (int)std::min<int64_t>((sz - hot + 3) / 4, 16384);
             hipLaunchKernelGGL(k_cold_index, dim3((unsigned)blocks), dim3(256), 0, h->compute, h->ptr, stage, k_lo, h->coord_of,
@@ -1520,12 +1535,12 @@ k_group_rows(const MAPP* __restrict__ map_prev, const float* __restrict__ val_pr
     // costs a third of the pass; nearly every row hits one of these).
     extern __shared__ unsigned long long hist[];
     float* dl = reinterpret_cast<float*>(hist + hot + k64);
-    // The workgroups walk the rows side by side: in iteration i workgroup b takes the ROW_TPB packs from
-    // (i * gridDim.x + b) * ROW_TPB on, so that at any time the whole grid works on one contiguous window of
+    // The workgroups walk the rows side by side: in iteration i workgroup b takes the blockDim.x packs from
+    // (i * gridDim.x + b) * blockDim.x on, so that at any time the whole grid works on one contiguous window of
     // every array (measured with a bare kernel of the same byte mix: 5.65 TB/s, against 5.0 TB/s when every
     // workgroup streams a slab of its own).
     const int64_t packs = (n + R - 1) / R;
-    const int64_t q_first = (int64_t)blockIdx.x * ROW_TPB + threadIdx.x, q_stride = (int64_t)gridDim.x * ROW_TPB;
+    const int64_t q_first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, q_stride = (int64_t)gridDim.x * blockDim.x;
     // All loads of an iteration are issued together, ahead of its first wait, and those of the first
     // iteration ahead of the set-up of the LDS tables (the loop below asks for the next pack's at its end.
     // Asking earlier was measured slower, with two packs per thread in turn by 3 % and with three, the
@@ -1566,9 +1581,9 @@ k_group_rows(const MAPP* __restrict__ map_prev, const float* __restrict__ val_pr
     };
     if (q_first < packs) request(q_first);
     if (HIST)
-        for (int i = threadIdx.x; i < hot + k64; i += ROW_TPB) hist[i] = 0ull;
+        for (int i = threadIdx.x; i < hot + k64; i += blockDim.x) hist[i] = 0ull;
     if (SCATTER)
-        for (int i = threadIdx.x; i <= kd; i += ROW_TPB) dl[i] = i < kd ? delta_prev[i] : 0.0f;   // [kd]: a zero for the rows without a step
+        for (int i = threadIdx.x; i <= kd; i += blockDim.x) dl[i] = i < kd ? delta_prev[i] : 0.0f;   // [kd]: a zero for the rows without a step
     __syncthreads();
     // the two longest coordinates of a group hold a quarter of its rows: their sums stay in
     // registers (one LDS update per wavefront at the end) instead of colliding in LDS
@@ -1576,7 +1591,7 @@ k_group_rows(const MAPP* __restrict__ map_prev, const float* __restrict__ val_pr
     // dense buffer of the short coordinates' rows (null: none): next position of this wavefront.  The
     // entries pass through a ring of 128 per wavefront in LDS and leave it 64 at a time, in one store
     // (written row by row they cost eight nearly empty stores per iteration).
-    uint32_t crun = (HIST && cbuf) ? __builtin_amdgcn_readfirstlane(wbase[blockIdx.x * (ROW_TPB / WAVE) + threadIdx.x / WAVE]) : 0u;
+    uint32_t crun = (HIST && cbuf) ? __builtin_amdgcn_readfirstlane(wbase[blockIdx.x * (int)(blockDim.x / WAVE) + threadIdx.x / WAVE]) : 0u;
     uint32_t cflushed = crun;
     float* stage = dl + kd + 1 + (threadIdx.x / WAVE) * COLD_RING;
     bool too_large = false;                    // ridge: a term outside the range the 64-bit sums are laid out for
@@ -1722,7 +1737,7 @@ k_group_rows(const MAPP* __restrict__ map_prev, const float* __restrict__ val_pr
         }
         __syncthreads();
         long long* out = partial + (size_t)blockIdx.x * (size_t)partial_stride;
-        for (int i = threadIdx.x; i < hot + k64; i += ROW_TPB) out[i] = (long long)hist[i];
+        for (int i = threadIdx.x; i < hot + k64; i += blockDim.x) out[i] = (long long)hist[i];
     }
     if (LOSS) {
         // the regulariser's sums over this workgroup's slice of the model (final by now: the last step kernel
@@ -1730,7 +1745,7 @@ k_group_rows(const MAPP* __restrict__ map_prev, const float* __restrict__ val_pr
         double sq = 0.0, ab = 0.0;
         const int64_t mper = (m + gridDim.x - 1) / gridDim.x;
         const int64_t m0 = min(m, (int64_t)blockIdx.x * mper), m1 = min(m, m0 + mper);
-        for (int64_t i = m0 + threadIdx.x; i < m1; i += ROW_TPB) {
+        for (int64_t i = m0 + threadIdx.x; i < m1; i += blockDim.x) {
             const double xi = (double)model[i];
             sq += xi * xi;
             ab += fabs(xi);
@@ -1749,7 +1764,7 @@ k_group_rows(const MAPP* __restrict__ map_prev, const float* __restrict__ val_pr
         __syncthreads();
         if (threadIdx.x < 3) {
             double t = 0.0;
-            for (int w = 0; w < ROW_TPB / WAVE; ++w) t += s_loss[3 * w + threadIdx.x];
+            for (int w = 0; w < (int)(blockDim.x / WAVE); ++w) t += s_loss[3 * w + threadIdx.x];
             loss_partial[3 * blockIdx.x + threadIdx.x] = t;
         }
     }
@@ -1890,15 +1905,39 @@ k_group_finish(const long long* __restrict__ partial, int64_t partial_stride, in
         }
     }
     if (rk < hot) {
-        if (!packed) {
-#pragma unroll 8
-            for (int w = part; w < n_wgs; w += STEP_PARTS) {
-                Gi += partial[(size_t)w * partial_stride + rk];
-                if (KIND == K_PRIMAL_LOGISTIC) Hi += partial[(size_t)w * partial_stride + k64 + rk];
+        // (eight loads under way together, whatever the number of workgroups: with a remainder taken one by one 245
+        // workgroups took 8.3 us, this way 4.6; the full 256 are read without the comparisons: 15.6 instead of 17.6 us for the
+        // categorical fields of 45.8 M rows)
+        constexpr int AHEAD = 8;
+        const bool whole = n_wgs % (AHEAD * STEP_PARTS) == 0;
+        if (whole && !packed) {
+            for (int w0 = part; w0 + (AHEAD - 1) * STEP_PARTS < n_wgs; w0 += AHEAD * STEP_PARTS)
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) {
+                    Gi += partial[(size_t)(w0 + u * STEP_PARTS) * partial_stride + rk];
+                    if (KIND == K_PRIMAL_LOGISTIC) Hi += partial[(size_t)(w0 + u * STEP_PARTS) * partial_stride + k64 + rk];
+                }
+        } else if (whole) {
+            for (int w0 = part; w0 + (AHEAD - 1) * STEP_PARTS < n_wgs; w0 += AHEAD * STEP_PARTS)
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u)
+                    Gi += partial[(size_t)(w0 + u * STEP_PARTS) * partial_stride + k64 + rk];   // whole words, modulo 2^64
+        }
+        for (int w0 = part; !whole && w0 < n_wgs; w0 += AHEAD * STEP_PARTS) {
+            long long a[AHEAD], b[AHEAD];
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                const int w = w0 + u * STEP_PARTS;
+                const long long* p = partial + (size_t)min(w, n_wgs - 1) * partial_stride + rk;
+                a[u] = p[packed ? k64 : 0];
+                b[u] = KIND == K_PRIMAL_LOGISTIC && !packed ? p[k64] : 0;
+                if (w >= n_wgs) a[u] = b[u] = 0;
             }
-        } else {
-#pragma unroll 8
-            for (int w = part; w < n_wgs; w += STEP_PARTS) Gi += partial[(size_t)w * partial_stride + k64 + rk];   // whole words, modulo 2^64
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                Gi += a[u];
+                Hi += b[u];
+            }
         }
     }
     sg[part][lr] = Gi;
@@ -2049,11 +2088,11 @@ static int grouped_epoch_kind(snap_handle* h) {
         // short coordinates through the dense buffer (only with a row pass that computes sums)
         const bool compact = !last && h->gcompact_host[g] && n > 0;
         const size_t lds = (size_t)(hot + k64) * sizeof(unsigned long long) + (size_t)(kd + 1) * sizeof(float) +
-                           (compact ? (size_t)(ROW_TPB / WAVE) * COLD_RING * sizeof(float) : 0);
+                           (compact ? (size_t)(h->g_row_tpb / WAVE) * COLD_RING * sizeof(float) : 0);
         const dim3 row_grid((unsigned)h->g_row_wgs);
         const bool scatter = prev >= 0, histo = !last && (hot > 0 || compact);
         float* cbuf = compact ? h->gcbuf : nullptr;
-        const uint32_t* wbase = compact ? h->gwbase + (size_t)g * (size_t)(h->g_row_wgs * (ROW_TPB / WAVE)) : nullptr;
+        const uint32_t* wbase = compact ? h->gwbase + (size_t)g * (size_t)(h->g_row_wgs * (h->g_row_tpb / WAVE)) : nullptr;
         if (streamed && !last) SNAP_TRY(acquire_map(h, (int)(gi % 3), sprof ? h->gev_prof[4 * gi + 2] : nullptr));
         else if (sprof) SNAP_HIP(hipEventRecord(h->gev_prof[4 * gi + 2], h->compute));
         if (n > 0 && (scatter || histo)) {
@@ -2078,23 +2117,23 @@ static int grouped_epoch_kind(snap_handle* h) {
                 const MC* mc = std::is_same<MC, uint8_t>::value ? (const MC*)(h->rowmap8 + (size_t)std::max(slot_c, 0) * h->n_pad)
                                                                 : (const MC*)map_cur;
                 if (scatter && histo)
-                    hipExtLaunchKernelGGL((k_group_rows<KIND, UNIT, true, true, MP, MC>), row_grid, dim3(ROW_TPB), lds, h->compute,
+                    hipExtLaunchKernelGGL((k_group_rows<KIND, UNIT, true, true, MP, MC>), row_grid, dim3(h->g_row_tpb), lds, h->compute,
                                           ev_a, ev_b, 0, mp, val_prev, delta_prev, mc, val_cur, hot, k64, vin, vout, h->y,
                                           h->ybits, n, gpart, h->gpartial_stride, scale, kd, h->status, cbuf, wbase, (double*)nullptr,
                                           (const float*)nullptr, (int64_t)0);
                 else if (scatter && last && h->g_want_loss) {
-                    hipExtLaunchKernelGGL((k_group_rows<KIND, UNIT, true, false, MP, MP, true>), row_grid, dim3(ROW_TPB), lds, h->compute,
+                    hipExtLaunchKernelGGL((k_group_rows<KIND, UNIT, true, false, MP, MP, true>), row_grid, dim3(h->g_row_tpb), lds, h->compute,
                                           ev_a, ev_b, 0, mp, val_prev, delta_prev, (const MP*)nullptr, val_cur, 0, 0, vin, vout, h->y,
                                           h->ybits, n, gpart, h->gpartial_stride, scale, kd, h->status, (float*)nullptr,
                                           (const uint32_t*)nullptr, h->gloss_partial, (const float*)h->x, h->m);
                     loss_done = true;
                 } else if (scatter)
-                    hipExtLaunchKernelGGL((k_group_rows<KIND, UNIT, true, false, MP, MP>), row_grid, dim3(ROW_TPB), lds, h->compute,
+                    hipExtLaunchKernelGGL((k_group_rows<KIND, UNIT, true, false, MP, MP>), row_grid, dim3(h->g_row_tpb), lds, h->compute,
                                           ev_a, ev_b, 0, mp, val_prev, delta_prev, (const MP*)nullptr, val_cur, 0, 0, vin, vout, h->y,
                                           h->ybits, n, gpart, h->gpartial_stride, scale, kd, h->status, (float*)nullptr,
                                           (const uint32_t*)nullptr, (double*)nullptr, (const float*)nullptr, (int64_t)0);
                 else
-                    hipExtLaunchKernelGGL((k_group_rows<KIND, UNIT, false, true, MC, MC>), row_grid, dim3(ROW_TPB), lds, h->compute,
+                    hipExtLaunchKernelGGL((k_group_rows<KIND, UNIT, false, true, MC, MC>), row_grid, dim3(h->g_row_tpb), lds, h->compute,
                                           ev_a, ev_b, 0, (const MC*)nullptr, val_prev, delta_prev, mc, val_cur, hot, k64, vin, vout, h->y,
                                           h->ybits, n, gpart, h->gpartial_stride, scale, kd, h->status, cbuf, wbase, (double*)nullptr,
                                           (const float*)nullptr, (int64_t)0);
@@ -2173,16 +2212,16 @@ static int grouped_dots_kind(snap_handle* h) {
         const int hot = h->ghot_host[g], k64 = h->gk64_host[g];
         const bool compact = h->gcompact_host[g] && n > 0;
         float* cbuf = compact ? h->gcbuf : nullptr;
-        const uint32_t* wbase = compact ? h->gwbase + (size_t)g * (size_t)(h->g_row_wgs * (ROW_TPB / WAVE)) : nullptr;
+        const uint32_t* wbase = compact ? h->gwbase + (size_t)g * (size_t)(h->g_row_wgs * (h->g_row_tpb / WAVE)) : nullptr;
         const MAPT* map_cur = streamed ? (const MAPT*)h->gring[gi % 3] : maps + (size_t)g * h->n_pad;
         if (streamed) SNAP_TRY(acquire_map(h, (int)(gi % 3), nullptr));
         if (n > 0 && (hot > 0 || compact)) {
             const size_t lds = (size_t)(hot + k64) * sizeof(unsigned long long) + sizeof(float) +
-                               (compact ? (size_t)(ROW_TPB / WAVE) * COLD_RING * sizeof(float) : 0);
+                               (compact ? (size_t)(h->g_row_tpb / WAVE) * COLD_RING * sizeof(float) : 0);
             const int slot_c = (!streamed && h->g8slot_host) ? h->g8slot_host[g] : -1;
             auto launch = [&](auto tag_c, const void* map) {
                 using MC = decltype(tag_c);
-                hipLaunchKernelGGL((k_group_rows<KIND, UNIT, false, true, MC, MC>), dim3((unsigned)h->g_row_wgs), dim3(ROW_TPB), lds,
+                hipLaunchKernelGGL((k_group_rows<KIND, UNIT, false, true, MC, MC>), dim3((unsigned)h->g_row_wgs), dim3(h->g_row_tpb), lds,
                                    h->compute, (const MC*)nullptr, (const float*)nullptr, (const float*)nullptr,
                                    (const MC*)map, UNIT ? (const float*)nullptr : h->rowval + (size_t)g * h->n_pad, hot,
                                    k64, h->v, h->v, h->y, h->ybits, n, gpart, h->gpartial_stride, scale, 0, h->status, cbuf,

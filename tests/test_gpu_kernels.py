@@ -271,3 +271,20 @@ def test_dual_epoch_with_the_shared_vector_in_lds(top, d, loss, in_flight):
             if in_flight == 1:
                 assert np.linalg.norm(alpha - o.x) <= 1e-4 * np.linalg.norm(o.x)
     assert abs(s.objective(want_dual=True)[1] - o.dual()) <= 1e-4 * abs(o.dual())
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("n", [2041, 2049, 40_009, 524_285, 524_293, 1_048_583])      # workgroups of 256, 512 and 1024 threads, their edges
+def test_group_sweeps_of_every_launch_shape(n, weighted):
+    ptr, idx, val, bounds = one_hot_columns(n, [64, 300, 5], 9, 0.05, weighted)
+    d, rng = bounds[-1], np.random.default_rng(10)
+    y = np.where(rng.random(n) < 0.3, 1.0, -1.0).astype(np.float32)
+    s = snap.Solver("csc", n, d, ptr, idx, val, y, "logistic", 1e-3, group_bounds=bounds)
+    o = oracle.Solver(oracle.Matrix("csc", n, d, ptr, idx, val), y, "logistic", 1e-3, chunk_bounds=bounds, shuffle_chunks=True)
+    for e in range(3):
+        s.epoch(e)
+        o.epoch(e)
+    x = s.model()[1]
+    assert np.linalg.norm(x - o.x) <= 2e-5 * np.linalg.norm(o.x)
+    P, D = s.objective(want_dual=True)
+    assert abs(P - o.primal()) <= 1e-5 * o.primal() and P >= D
