@@ -225,23 +225,30 @@ k_tile_solve(const float* __restrict__ partial, int n_wg, int64_t c0, int nb, ui
     uint32_t* keys = reinterpret_cast<uint32_t*>(gfin + TILE_B);
     int* seq_lds = reinterpret_cast<int*>(keys + TILE_B);
     static_assert(sizeof(double) * (SOLVE_PARTS + 1) * TILE_B + 8 * TILE_B <= sizeof(float) * TILE_B * TILE_B, "fits");
-    uint32_t my_key = 0;
     if (threadIdx.x < TILE_B) {
         double acc = 0.0;
         for (int q = 0; q < SOLVE_PARTS; ++q) acc += gs[q * TILE_B + threadIdx.x];
         gfin[threadIdx.x] = acc;
-        my_key = perm_key(perm_key_base(seed, tile), threadIdx.x);
-        keys[threadIdx.x] = my_key;
+        keys[threadIdx.x] = perm_key(perm_key_base(seed, tile), threadIdx.x);
     }
     __syncthreads();
-    // position in the visiting order: rank of (key, index) among the tile's coordinates
-    if ((int)threadIdx.x < nb) {
-        int rank = 0;
-        for (int o = 0; o < nb; ++o) {
-            const uint32_t ko = keys[o];
-            rank += (ko < my_key || (ko == my_key && o < (int)threadIdx.x)) ? 1 : 0;
+    // position in the visiting order: rank of (key, index) among the tile's coordinates, eight lanes per coordinate
+    {
+        static_assert(SOLVE_TPB == 8 * TILE_B, "eight lanes per coordinate");
+        const int b = threadIdx.x / 8, sub = threadIdx.x % 8;
+        if (b < nb) {
+            const uint32_t kb = keys[b];
+            int rank = 0;
+#pragma unroll 4
+            for (int o = sub; o < nb; o += 8) {
+                const uint32_t ko = keys[o];
+                rank += (ko < kb || (ko == kb && o < b)) ? 1 : 0;
+            }
+            rank += __shfl_xor(rank, 1, WAVE);
+            rank += __shfl_xor(rank, 2, WAVE);
+            rank += __shfl_xor(rank, 4, WAVE);
+            if (sub == 0) seq_lds[rank] = b;
         }
-        seq_lds[rank] = threadIdx.x;
     }
     __syncthreads();
     const int lane = threadIdx.x & (WAVE - 1);
