@@ -649,6 +649,9 @@ k_scd_lds(ChunkView cv, const uint32_t* __restrict__ order, int64_t n_small, con
 #pragma unroll
         for (int j = 0; j < REGS; ++j) asm volatile("" : "+v"(cur.raw[j]), "+v"(cur.a[j]));
         __builtin_amdgcn_sched_barrier(0);
+        // (one long coordinate must not make all others pay for its registers: four at a time are passed over)
+        const int len0 = R == 1 && REGS > 4 ? __builtin_amdgcn_readlane(cur.len, 0) : 0;
+        auto used = [&](int j) { return !(R == 1 && REGS > 4) || j < 4 || (j & ~3) * WAVE < len0; };
         float yy[REGS];
         bool have[REGS];
         double vv[REGS];
@@ -657,7 +660,8 @@ k_scd_lds(ChunkView cv, const uint32_t* __restrict__ order, int64_t n_small, con
             have[j] = place(j) < Shape::spread(cur.len, j, upper);
             yy[j] = 0.0f;
             if (KIND == K_PRIMAL_LOGISTIC) yy[j] = (cur.raw[j] & LABEL_BIT) ? -1.0f : 1.0f;
-            vv[j] = s_shared[cur.raw[j] & IDX_MASK];
+            vv[j] = 0.0;
+            if (used(j)) vv[j] = s_shared[cur.raw[j] & IDX_MASK];
         }
         entry4 = load_entry(g + 4 * n_waves);
         range3 = load_range(g + 3 * n_waves, entry3);
@@ -667,7 +671,7 @@ k_scd_lds(ChunkView cv, const uint32_t* __restrict__ order, int64_t n_small, con
 #pragma unroll
         for (int j = 0; j < REGS; ++j) {
             pg[j] = ph[j] = 0.0f;
-            if (have[j]) accumulate<KIND>(cur.a[j], (float)vv[j], yy[j], pg[j], ph[j]);
+            if (used(j) && have[j]) accumulate<KIND>(cur.a[j], (float)vv[j], yy[j], pg[j], ph[j]);
         }
         float gs = sum_rows<S, R>(pg, lane), hs = 0.0f;
         if (KIND == K_PRIMAL_LOGISTIC) hs = sum_rows<S, R>(ph, lane);
@@ -680,6 +684,7 @@ k_scd_lds(ChunkView cv, const uint32_t* __restrict__ order, int64_t n_small, con
         if (__ballot(mult != 0.0f) != 0) {
 #pragma unroll
             for (int j = 0; j < REGS; ++j) {
+                if (!used(j)) continue;
                 const float mj = __int_as_float(Shape::spread(__float_as_int(mult), j, upper));
                 if (have[j] && mj != 0.0f) unsafeAtomicAdd(&s_shared[cur.raw[j] & IDX_MASK], (double)(mj * cur.a[j]));
             }
@@ -952,7 +957,7 @@ static int launch_kind(snap_handle* h, const ChunkView& cv, const snap_handle::C
         // nonzeros takes 0.10 us of the one compute unit and 1.4 us / (columns in flight) otherwise: equal at 14.  Longer
         // columns (up to 1 024) shift both sides alike.
         const int64_t few = KIND == K_DUAL ? 95 : 14;
-        if (h->step_prep && waves <= few && h->max_small_len <= 1024) {
+        if (h->step_prep && waves <= few && h->max_small_len <= 1024 && ck.nnz1 > ck.nnz0) {     // (idle lanes load the chunk's first nonzero)
             if (KIND != K_PRIMAL_LOGISTIC)
                 hipLaunchKernelGGL((k_prepare_steps<KIND>), dim3((unsigned)std::min<int64_t>((cv.c1 - cv.c0 + 255) / 256, 1024)), dim3(256), 0,
                                    h->compute, cv.c0, cv.c1, h->x, h->norms, h->y, sp, (double2*)h->step_prep);
@@ -964,6 +969,7 @@ static int launch_kind(snap_handle* h, const ChunkView& cv, const snap_handle::C
             if (h->max_small_len <= 32 && waves >= 8) launch(k_scd_lds<KIND, 32, 8>, lds_waves(32), 8);
             else if (h->max_small_len <= 64 && waves >= 4) launch(k_scd_lds<KIND, 64, 4>, lds_waves(64), 4);
             else if (h->max_small_len <= 256) launch(k_scd_lds<KIND, 256, 1>, lds_waves(256), 1);
+            else if (h->max_small_len <= 512) launch(k_scd_lds<KIND, 512, 1>, lds_waves(512), 1);
             else launch(k_scd_lds<KIND, 1024, 1>, lds_waves(1024), 1);
             SNAP_HIP(hipGetLastError());
             return SNAP_OK;

@@ -217,7 +217,7 @@ def test_epoch_order_of_two_classes_and_of_more_coordinates_than_buckets_take(ho
 
 
 @pytest.mark.parametrize("loss", ["ridge", "logistic", "elastic"])
-@pytest.mark.parametrize("n,d,top", [(300, 40, 32), (300, 40, 64), (900, 257, 250), (20_000, 64, 1024), (4_000, 30, 1025), (20_480, 33, 90), (20_481, 33, 90)])
+@pytest.mark.parametrize("n,d,top", [(300, 40, 32), (300, 40, 64), (900, 257, 250), (900, 100, 257), (20_000, 64, 1024), (4_000, 30, 1025), (20_480, 33, 90), (20_481, 33, 90)])
 @pytest.mark.parametrize("in_flight", [1, 12])             # coordinates; one: exactly the sequential epoch
 def test_primal_epoch_with_the_shared_vector_in_lds(n, d, top, loss, in_flight):
     rng = np.random.default_rng(n + top)
